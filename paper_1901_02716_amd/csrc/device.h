@@ -198,6 +198,14 @@ __device__ __forceinline__ float recip_f32(float x) {
   return __builtin_fmaf(r, e, r);
 }
 
+template <class T>
+__device__ __forceinline__ T recip(T x) {
+  if constexpr (sizeof(T) == 4)
+    return recip_f32(x);
+  else
+    return (T)1 / x;
+}
+
 // x / 36 for the link sums, which carry the weights times 36: the product
 // with the rounded constant 1/36 (which is 2.4e-8 too large in FP32) is
 // corrected by one residual step, so that no bias of that size is applied to

@@ -98,6 +98,17 @@ int fast_candidates(const Layout& L, const StepParams& p, int cus, FastShape* ou
 hipError_t launch_step_fast(const Layout& L, const void* src, void* dst, const StepParams& p, const FastShape& sh,
                             hipStream_t s);
 
+// FP64 D3Q19 path (kernels_seg.hip), the general kernel's form for FP64: rows
+// of any width cut into segments of 64 kx nodes, workgroups of w output rows,
+// nyb x nzb of them per segment.
+struct Seg3DShape {
+  int kx = 1, w = 6, nyb = 1, nzb = 1;
+};
+bool seg3d_supported(const Layout& L);
+Seg3DShape seg3d_shape(const Layout& L, const StepParams& p, int cus);
+hipError_t launch_step_seg(const Layout& L, const void* src, void* dst, const StepParams& p, const Seg3DShape& sh,
+                           hipStream_t s);
+
 // Fast D2Q9 path (kernels_2d.hip): one wavefront per (x-segment of 64*kx
 // nodes, band of rows); nband bands per segment.
 struct Fast2DShape {

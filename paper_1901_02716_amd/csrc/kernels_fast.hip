@@ -24,9 +24,8 @@
 //  - Workgroups are numbered so that each XCD gets a contiguous band of tiles
 //    (neighbouring tiles share halo rows through that XCD's L2); rows that no
 //    other workgroup reads are loaded non-temporally, to leave L2 to those.
+#include "d3q19.h"
 #include "internal.h"
-
-#include <type_traits>
 
 namespace maclab {
 
@@ -44,11 +43,6 @@ struct Fast3DParams {
 };
 
 // ----------------------------------------------------------- row load/store
-template <class C, int KX>
-struct alignas(sizeof(typename C::elem) * KX) RowVec {
-  typename C::elem v[KX];
-};
-
 // Loads one row of one field as stored (times the codec's storage scale).
 template <class C, int KX>
 __device__ __forceinline__ void load_row(const typename C::elem* __restrict__ p, int field, float (&out)[KX]) {
@@ -85,144 +79,16 @@ __device__ __forceinline__ void store_row(typename C::elem* __restrict__ p, cons
   }
 }
 
-template <int KX>
-struct PlaneAcc {
-  float r[KX], mx[KX], my[KX], mz[KX];  // 36 * (drho', m')
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int e = 0; e < KX; ++e) r[e] = mx[e] = my[e] = mz[e] = 0.f;
-  }
-};
-
-// Finalises the KX nodes of one row of destination plane accumulators a and
-// encodes them: drho' = r / 36 and u~' = (m + 36 g) / (36 rho_ref + r)
-// (Eqs. (4)-(5) with the sums carried times 36). The accumulators hold the
-// sums times K = the codec's density scale (a power of two; see node_links),
-// so K drho' = div36(a.r) and S u~' = S (a.m + 36 K g) / (36 K rho_ref + a.r)
-// for the velocity scale S: every scale is exact, and the stored values
-// carry them. Node e of the lane (dense node index node0 + e) draws its own
-// rounding bits, sr_node_bits(key, node0 + e), the bits every kernel gives
-// that node in that step, so the rounding decisions of neighbouring nodes are
-// independent.
-template <class C, int KX>
-__device__ __forceinline__ void finalize_row(const PlaneAcc<KX>& a, float rho_ref, float g36x, float g36y, float g36z,
-                                             uint32_t key, int64_t node0, RowVec<C, KX> (&o)[4]) {
-#pragma clang fp contract(off)
-  constexpr float K = C::kScaleRho;
-  float v[4][KX];
-  uint32_t bits[KX];
-#pragma unroll
-  for (int e = 0; e < KX; ++e) {
-    const float inv = recip_f32(K * (36.f * rho_ref) + a.r[e]) * C::kScaleU;
-    v[0][e] = div36(a.r[e]);
-    v[1][e] = (a.mx[e] + K * g36x) * inv;
-    v[2][e] = (a.my[e] + K * g36y) * inv;
-    v[3][e] = (a.mz[e] + K * g36z) * inv;
-    bits[e] = needs_rng<C>::value ? sr_node_bits(key, node0 + e) : 0u;
-  }
-  if constexpr (sizeof(typename C::elem) == 2 && KX % 2 == 0) {
-    struct Words { uint32_t w[KX / 2]; };
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      Words w;
-#pragma unroll
-      for (int e = 0; e < KX; e += 2) w.w[e / 2] = C::enc2_scaled(v[f][e], v[f][e + 1], f, bits[e], bits[e + 1]);
-      o[f] = __builtin_bit_cast(RowVec<C, KX>, w);
-    }
-  } else {
-#pragma unroll
-    for (int f = 0; f < 4; ++f)
-#pragma unroll
-      for (int e = 0; e < KX; ++e) o[f].v[e] = C::enc_scaled(v[f][e], f, bits[e]);
-  }
-}
-
-// The 19 link values of one node, times 36, in deviation form (Eq. (2)):
-//   36 F^_a = wnum_a [a + c.b + sum_i c_i^2 q_ii + sum_{i<j} c_i c_j q_ij]
-// with a = drho - 1.5 rho |u|^2, b = 3 rho u, q_ii = 4.5 rho u_i^2,
-// q_ij = 9 rho u_i u_j. The six axis links are carried halved (h = F/2).
-struct Links {
-  float f0, hxp, hxm, hyp, hym, hzp, hzm;
-  float pp0, mm0, pm0, mp0;  // (1,1,0) (-1,-1,0) (1,-1,0) (-1,1,0)
-  float p0p, m0m, p0m, m0p;  // (1,0,1) (-1,0,-1) (1,0,-1) (-1,0,1)
-  float zpp, zmm, zpm, zmp;  // (0,1,1) (0,-1,-1) (0,1,-1) (0,-1,1)
-};
-
-// Contraction is off and every FMA is written out, so a link value has the
-// same bits whichever wavefront (output or halo row) computes it and the
-// result does not depend on the tiling.
-//
-// The inputs are the stored fields times the codec's storage scales, d =
-// K drho and v = S u~ (K, S powers of two; 1 for FP32 storage), and every
-// link value comes out times K: with r3 = (3 K / S) rho each b and each
-// product c_ij = b_i v_j carries K resp. K S, and the constants that multiply
-// the c_ij are divided by S. Powers of two commute with every rounding, so
-// the scaled links are K times the unscaled ones, bit for bit.
-template <class C>
-__device__ __forceinline__ void node_links(float dr, float ux, float uy, float uz, float rho_ref, Links& L) {
-#pragma clang fp contract(off)
-  constexpr float K = C::kScaleRho, S = C::kScaleU;
-  const float rho = K == 1.f ? rho_ref + dr : __builtin_fmaf(dr, 1.f / K, rho_ref);
-  const float r3 = (3.f * K / S) * rho;
-  const float bx = r3 * ux, by = r3 * uy, bz = r3 * uz;    // 3 rho u          (times K)
-  const float cxx = bx * ux, cyy = by * uy, czz = bz * uz;  // 3 rho u_i^2      (times K S; q_ii = 1.5 c_ii)
-  const float cxy = bx * uy, cxz = bx * uz, cyz = by * uz;  // 3 rho u_i u_j    (times K S; q_ij = 3 c_ij)
-  const float a = __builtin_fmaf((cxx + cyy) + czz, -0.5f / S, dr);
-  const float sx = __builtin_fmaf(cxx, 1.5f / S, a), sy = __builtin_fmaf(cyy, 1.5f / S, a),
-              sz = __builtin_fmaf(czz, 1.5f / S, a);
-  L.f0 = 12.f * a;
-  L.hxp = sx + bx;
-  L.hxm = sx - bx;
-  L.hyp = sy + by;
-  L.hym = sy - by;
-  L.hzp = sz + bz;
-  L.hzm = sz - bz;
-  float t, p, m, u, v;
-  t = __builtin_fmaf(cyy, 1.5f / S, sx);  // a + q_xx + q_yy
-  p = __builtin_fmaf(cxy, 3.f / S, t);
-  m = __builtin_fmaf(cxy, -3.f / S, t);
-  u = bx + by;
-  v = bx - by;
-  L.pp0 = p + u;
-  L.mm0 = p - u;
-  L.pm0 = m + v;
-  L.mp0 = m - v;
-  t = __builtin_fmaf(czz, 1.5f / S, sx);  // a + q_xx + q_zz
-  p = __builtin_fmaf(cxz, 3.f / S, t);
-  m = __builtin_fmaf(cxz, -3.f / S, t);
-  u = bx + bz;
-  v = bx - bz;
-  L.p0p = p + u;
-  L.m0m = p - u;
-  L.p0m = m + v;
-  L.m0p = m - v;
-  t = __builtin_fmaf(czz, 1.5f / S, sy);  // a + q_yy + q_zz
-  p = __builtin_fmaf(cyz, 3.f / S, t);
-  m = __builtin_fmaf(cyz, -3.f / S, t);
-  u = by + bz;
-  v = by - bz;
-  L.zpp = p + u;
-  L.zmm = p - u;
-  L.zpm = m + v;
-  L.zmp = m - v;
-}
-
 // Pushes one source row (the KX nodes of this lane).
 // MODE 0 (output row): c_y = 0 links go into the plane accumulators of this
 // wavefront -- am (destination plane z-1), ac (plane z), ap (plane z+1, which
 // this call is the first to touch, so it is assigned) -- and c_y = +-1 links
 // into this wavefront's LDS rows. MODE 1 / 2 (halo row below / above the
 // tile): only the c_y = +1 / -1 links, to LDS.
-template <int KX>
-__device__ __forceinline__ void own_row_links(const float (&f0)[KX], const float (&hzp)[KX], const float (&hzm)[KX],
-                                              const float (&hxp)[KX], const float (&p0p)[KX], const float (&p0m)[KX],
-                                              const float (&hxm)[KX], const float (&m0p)[KX], const float (&m0m)[KX],
-                                              PlaneAcc<KX>& am, PlaneAcc<KX>& ac, PlaneAcc<KX>& ap);
-
 template <class C, int KX, int MODE>
 __device__ __forceinline__ void push_row(const float (&dr)[KX], const float (&ux)[KX], const float (&uy)[KX],
-                                         const float (&uz)[KX], float rho_ref, PlaneAcc<KX>& am,
-                                         PlaneAcc<KX>& ac, PlaneAcc<KX>& ap, float* __restrict__ up,
+                                         const float (&uz)[KX], float rho_ref, PlaneAcc<float, KX>& am,
+                                         PlaneAcc<float, KX>& ac, PlaneAcc<float, KX>& ap, float* __restrict__ up,
                                          float* __restrict__ dn, int lane) {
 #pragma clang fp contract(off)
   constexpr int NX = 64 * KX;
@@ -235,7 +101,7 @@ __device__ __forceinline__ void push_row(const float (&dr)[KX], const float (&ux
   float hym[KX], pm0[KX], mm0[KX], zmp[KX], zmm[KX];
 #pragma unroll
   for (int e = 0; e < KX; ++e) {
-    Links L;
+    Links<float> L;
     node_links<C>(dr[e], ux[e], uy[e], uz[e], rho_ref, L);
     hyp[e] = L.hyp;
     pp0[e] = L.pp0;
@@ -278,43 +144,7 @@ __device__ __forceinline__ void push_row(const float (&dr)[KX], const float (&ux
   };
   if constexpr (MODE != 2) send(up, hyp, pp0, mp0, zpp, zpm);
   if constexpr (MODE != 1) send(dn, hym, pm0, mm0, zmp, zmm);
-  if constexpr (MODE == 0) own_row_links<KX>(f0, hzp, hzm, hxp, p0p, p0m, hxm, m0p, m0m, am, ac, ap);
-}
-
-// The c_y = 0 links of a row into the plane accumulators: rest, +-z, and the
-// links moving in x, which cross to the neighbouring lane at the lane edges.
-// Plane z+1 (ap) is first touched here, so it is assigned.
-template <int KX>
-__device__ __forceinline__ void own_row_links(const float (&f0)[KX], const float (&hzp)[KX], const float (&hzm)[KX],
-                                              const float (&hxp)[KX], const float (&p0p)[KX], const float (&p0m)[KX],
-                                              const float (&hxm)[KX], const float (&m0p)[KX], const float (&m0m)[KX],
-                                              PlaneAcc<KX>& am, PlaneAcc<KX>& ac, PlaneAcc<KX>& ap) {
-#pragma clang fp contract(off)
-  const float in_hxp = dpp_from_left(hxp[KX - 1]), in_p0p = dpp_from_left(p0p[KX - 1]),
-              in_p0m = dpp_from_left(p0m[KX - 1]);
-  const float in_hxm = dpp_from_right(hxm[0]), in_m0p = dpp_from_right(m0p[0]), in_m0m = dpp_from_right(m0m[0]);
-#pragma unroll
-  for (int d = 0; d < KX; ++d) {
-    // links arriving at node d from d-1 (moving +x) and d+1 (moving -x)
-    const float Phx = d > 0 ? hxp[d - 1] : in_hxp, Pzp = d > 0 ? p0p[d - 1] : in_p0p,
-                Pzm = d > 0 ? p0m[d - 1] : in_p0m;
-    const float Mhx = d < KX - 1 ? hxm[d + 1] : in_hxm, Mzp = d < KX - 1 ? m0p[d + 1] : in_m0p,
-                Mzm = d < KX - 1 ? m0m[d + 1] : in_m0m;
-    // plane z: rest and +-x
-    const float A = Phx + Mhx, B = Phx - Mhx;
-    ac.r[d] += __builtin_fmaf(2.f, A, f0[d]);
-    ac.mx[d] = __builtin_fmaf(2.f, B, ac.mx[d]);
-    // plane z+1: +z, +x+z, -x+z (first contributions to this plane)
-    const float sp = __builtin_fmaf(2.f, hzp[d], Pzp + Mzp);
-    ap.r[d] = sp;
-    ap.mz[d] = sp;
-    ap.mx[d] = Pzp - Mzp;
-    // plane z-1: -z, +x-z, -x-z
-    const float sm = __builtin_fmaf(2.f, hzm[d], Pzm + Mzm);
-    am.r[d] += sm;
-    am.mz[d] -= sm;
-    am.mx[d] += Pzm - Mzm;
-  }
+  if constexpr (MODE == 0) own_row_links<float, KX>(f0, hzp, hzm, hxp, p0p, p0m, hxm, m0p, m0m, am, ac, ap);
 }
 
 // Adds the c_y = +1 links arriving from the row below (S = +1) or the c_y =
@@ -324,7 +154,7 @@ __device__ __forceinline__ void own_row_links(const float (&f0)[KX], const float
 // momentum of plane z+1 is first touched by the row below, so it is assigned.
 template <int KX, int S>
 __device__ __forceinline__ void add_row_links(float h, float ep_from_left, float em_from_right, float vp, float vm,
-                                              int d, PlaneAcc<KX>& am, PlaneAcc<KX>& ac, PlaneAcc<KX>& ap) {
+                                              int d, PlaneAcc<float, KX>& am, PlaneAcc<float, KX>& ac, PlaneAcc<float, KX>& ap) {
 #pragma clang fp contract(off)
   const float s = __builtin_fmaf(2.f, h, ep_from_left + em_from_right);
   ac.r[d] += s;
@@ -344,41 +174,16 @@ __device__ __forceinline__ void add_row_links(float h, float ep_from_left, float
   }
 }
 
-// Adds the contributions sent through LDS by the rows below (c_y = +1 links,
-// S = +1) and above (c_y = -1 links, S = -1): s and d in the plane of the
-// source, vp / vm moving to planes z+1 / z-1. The y momentum of plane z+1 is
-// first touched by the row below, so it is assigned.
-template <int KX, int S>
-__device__ __forceinline__ void add_sent(float s, float d, float vp, float vm, int e, PlaneAcc<KX>& am,
-                                         PlaneAcc<KX>& ac, PlaneAcc<KX>& ap) {
-#pragma clang fp contract(off)
-  ac.r[e] += s;
-  ac.mx[e] += d;
-  ap.r[e] += vp;
-  ap.mz[e] += vp;
-  am.r[e] += vm;
-  am.mz[e] -= vm;
-  if constexpr (S > 0) {
-    ac.my[e] += s;
-    ap.my[e] = vp;
-    am.my[e] += vm;
-  } else {
-    ac.my[e] -= s;
-    ap.my[e] -= vp;
-    am.my[e] -= vm;
-  }
-}
-
 template <int KX>
 __device__ __forceinline__ void pull_rows(const float* __restrict__ from_below, const float* __restrict__ from_above,
-                                          PlaneAcc<KX>& am, PlaneAcc<KX>& ac, PlaneAcc<KX>& ap, int lane) {
+                                          PlaneAcc<float, KX>& am, PlaneAcc<float, KX>& ac, PlaneAcc<float, KX>& ap, int lane) {
   constexpr int NX = 64 * KX;
 #pragma unroll
   for (int e = 0; e < KX; ++e) {
     const int x = e * 64 + lane;
-    add_sent<KX, 1>(from_below[0 * NX + x], from_below[1 * NX + x], from_below[2 * NX + x], from_below[3 * NX + x], e,
+    add_sent<float, KX, 1>(from_below[0 * NX + x], from_below[1 * NX + x], from_below[2 * NX + x], from_below[3 * NX + x], e,
                     am, ac, ap);
-    add_sent<KX, -1>(from_above[0 * NX + x], from_above[1 * NX + x], from_above[2 * NX + x], from_above[3 * NX + x], e,
+    add_sent<float, KX, -1>(from_above[0 * NX + x], from_above[1 * NX + x], from_above[2 * NX + x], from_above[3 * NX + x], e,
                      am, ac, ap);
   }
 }
@@ -387,23 +192,6 @@ template <int KX>
 struct RowData {
   float dr[KX], ux[KX], uy[KX], uz[KX];
 };
-
-// Raw (stored) elements of one row of the four fields.
-template <class C, int KX>
-struct RawRow {
-  RowVec<C, KX> f[4];
-};
-
-// c ? a : b on the bit patterns. A plain conditional between two elements of
-// one row is turned by the compiler into a load at a selected index, which
-// puts 16-bit rows in scratch memory.
-template <class E>
-__device__ __forceinline__ E pick_bits(bool c, E a, E b) {
-  using U = std::conditional_t<sizeof(E) == 2, uint16_t, std::conditional_t<sizeof(E) == 4, uint32_t, uint64_t>>;
-  static_assert(sizeof(U) == sizeof(E), "element size");
-  const U m = (U)0 - (U)c;
-  return __builtin_bit_cast(E, (U)((__builtin_bit_cast(U, a) & m) | (__builtin_bit_cast(U, b) & (U)~m)));
-}
 
 // PF: source planes loaded ahead (1 or 2).
 //
@@ -523,7 +311,7 @@ __global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_fast(const typename C
   // LDS, then finalise destination plane zs-1 (STORE) or issue the same stores
   // out of range. am / ac / ap are the accumulators of destination planes
   // zs-1, zs, zs+1; b holds plane zs and is refilled with plane zs+PF.
-  auto source_plane = [&](auto store_c, int zs, PlaneAcc<KX>& am, PlaneAcc<KX>& ac, PlaneAcc<KX>& ap,
+  auto source_plane = [&](auto store_c, int zs, PlaneAcc<float, KX>& am, PlaneAcc<float, KX>& ac, PlaneAcc<float, KX>& ap,
                           RawRow<C, KX>& b, int set) {
     constexpr bool STORE = decltype(store_c)::value;
     const int so = DB ? set * SLOTS : 0;
@@ -600,7 +388,7 @@ __global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_fast(const typename C
   // plane zs.
   using NoStore = std::integral_constant<bool, false>;
   using Store = std::integral_constant<bool, true>;
-  PlaneAcc<KX> a0, a1, a2;
+  PlaneAcc<float, KX> a0, a1, a2;
   a0.zero();
   a1.zero();
   RawRow<C, KX> b0, b1;
@@ -637,12 +425,12 @@ __global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_fast(const typename C
 // that reach it. Link values and the order of every sum are those of the
 // exchange kernel above, so both kernels give the same bits.
 template <class C, int KX, int S>
-__device__ __forceinline__ void neighbour_row(const RowData<KX>& b, float rho_ref, PlaneAcc<KX>& am,
-                                              PlaneAcc<KX>& ac, PlaneAcc<KX>& ap) {
+__device__ __forceinline__ void neighbour_row(const RowData<KX>& b, float rho_ref, PlaneAcc<float, KX>& am,
+                                              PlaneAcc<float, KX>& ac, PlaneAcc<float, KX>& ap) {
   float h[KX], ep[KX], em[KX], vp[KX], vm[KX];
 #pragma unroll
   for (int e = 0; e < KX; ++e) {
-    Links L;
+    Links<float> L;
     node_links<C>(b.dr[e], b.ux[e], b.uy[e], b.uz[e], rho_ref, L);
     if constexpr (S > 0) {
       h[e] = L.hyp;
@@ -697,12 +485,12 @@ __global__ __launch_bounds__(64 * NWV) void step_d3q19_indep(const typename C::e
   };
 
   RowData<KX> own, below, above;
-  auto source_plane = [&](int zs, PlaneAcc<KX>& am, PlaneAcc<KX>& ac, PlaneAcc<KX>& ap) {
+  auto source_plane = [&](int zs, PlaneAcc<float, KX>& am, PlaneAcc<float, KX>& ac, PlaneAcc<float, KX>& ap) {
     {
       float f0[KX], hzp[KX], hzm[KX], hxp[KX], p0p[KX], p0m[KX], hxm[KX], m0p[KX], m0m[KX];
 #pragma unroll
       for (int e = 0; e < KX; ++e) {
-        Links L;
+        Links<float> L;
         node_links<C>(own.dr[e], own.ux[e], own.uy[e], own.uz[e], p.rho_ref, L);
         f0[e] = L.f0;
         hzp[e] = L.hzp;
@@ -715,7 +503,7 @@ __global__ __launch_bounds__(64 * NWV) void step_d3q19_indep(const typename C::e
         m0m[e] = L.m0m;
       }
       if (zs < z1) load(y, zs + 1, own);
-      own_row_links<KX>(f0, hzp, hzm, hxp, p0p, p0m, hxm, m0p, m0m, am, ac, ap);
+      own_row_links<float, KX>(f0, hzp, hzm, hxp, p0p, p0m, hxm, m0p, m0m, am, ac, ap);
     }
     neighbour_row<C, KX, 1>(below, p.rho_ref, am, ac, ap);
     if (zs < z1) load(yb, zs + 1, below);
@@ -731,7 +519,7 @@ __global__ __launch_bounds__(64 * NWV) void step_d3q19_indep(const typename C::e
     }
   };
 
-  PlaneAcc<KX> a0, a1, a2;
+  PlaneAcc<float, KX> a0, a1, a2;
   a0.zero();
   a1.zero();
   load(y, z0 - 1, own);

@@ -23,6 +23,8 @@ struct Plan {
   int kernel = 0;
   FastShape s3;
   Fast2DShape s2;
+  Seg3DShape seg;      // kernel 0, FP64 D3Q19: its tiling, by the rule of seg3d_shape ...
+  int seg_fixed = -1;  // ... for these face kinds (bit k: axis k is bounded)
 };
 }  // namespace
 
@@ -293,14 +295,24 @@ hipError_t launch_plan(const Layout& L, const StepParams& p, const Plan& pl, con
     case 2: return launch_step_fast(L, src, dst, p, pl.s3, s);
     case 3: return launch_step_fast2d(L, src, dst, p, pl.s2, s);
   }
-  return launch_step_generic(L, src, dst, p, s);
+  return pl.seg_fixed >= 0 ? launch_step_seg(L, src, dst, p, pl.seg, s) : launch_step_generic(L, src, dst, p, s);
+}
+
+// The tiling of the FP64 D3Q19 kernel for the lattice's current faces.
+void set_seg(const Layout& L, const StepParams& p, int cus, Plan* pl) {
+  const int fixed = (p.fixed[0] != 0) | (p.fixed[1] != 0) << 1 | (p.fixed[2] != 0) << 2;
+  if (pl->kernel != 0 || !seg3d_supported(L) || pl->seg_fixed == fixed) return;
+  pl->seg = seg3d_shape(L, p, cus);
+  pl->seg_fixed = fixed;
 }
 
 const Plan& current_plan(maclab_t h, const StepParams& p) {
   if (!(h->plan_set && plan_valid(h->L, p, h->plan))) {
-    h->plan = plan_default(h->L, p, h->cus);
+    const Plan pl = plan_default(h->L, p, h->cus);
+    if (pl.kernel != 0 || h->plan.kernel != 0) h->plan = pl;  // (the general kernel's tiling is kept while it runs)
     h->plan_set = false;
   }
+  set_seg(h->L, p, h->cus, &h->plan);
   return h->plan;
 }
 
@@ -644,6 +656,7 @@ int maclab_autotune(maclab_t h, int reps, double* best_ms) {
   void* dst = h->state[h->cur ^ 1];  // scratch output: the state is not advanced
   Plan cand[96];
   const int nc = plan_candidates(h->L, p, h->cus, cand, 96);
+  for (int i = 0; i < nc; ++i) set_seg(h->L, p, h->cus, &cand[i]);
   hipEvent_t e0, e1;
   HIP_TRY(h, hipEventCreate(&e0));
   hipError_t ee = hipEventCreate(&e1);
