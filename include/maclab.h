@@ -127,6 +127,10 @@ int maclab_set_fields(maclab_t h, const double* rho, const double* u, int on_dev
 
 /* Enqueues n time steps (Eqs. (4)-(5) plus the body force of test 2: the
  * new lattice velocity is (sum_a c_a f_eq_a + dt G / e) / rho'). Asynchronous.
+ * D2Q9 lattices with periodic and fixed faces take several steps per launch
+ * (a tile of the lattice is advanced in registers), with the bits of single
+ * steps; the last step of a call is a launch of its own, so that the other
+ * buffer holds the state one step before (maclab_residual).
  * Returns MACLAB_EINVAL if the face kinds of an axis differ. */
 int maclab_step(maclab_t h, int64_t n);
 
@@ -184,7 +188,8 @@ int maclab_save_state(maclab_t h, void* dst_device);
 int maclab_load_state(maclab_t h, const void* src_device);
 
 /* Kernel and tiling of the step. out[5] = {kernel, W, nyb, nzb, pf}.
- *  kernel 0: general kernel (any shape and boundaries; no tiling).
+ *  kernel 0: general kernel (any shape and boundaries; no tiling to set; FP64
+ *    D3Q19 runs it as row segments with an LDS exchange).
  *  kernel 1: fast D3Q19, LDS exchange (row pitch 64, 128 or 256: x extent
  *    64, 128 or 256, or between fixed x faces an extent padded to one of
  *    them; FP32 arithmetic): one wavefront per x-row marches in z;
@@ -203,7 +208,9 @@ int maclab_load_state(maclab_t h, const void* src_device);
  * set_tiling validates (nyb <= rows, nzb <= planes or bands <= rows) and
  * returns MACLAB_EUNSUPPORTED when the kernel does not handle the lattice.
  * Kernels 1 and 2 and every valid tiling of a kernel give bitwise identical
- * results. */
+ * results. A tiling of kernel 3 that was set runs one step per launch; the
+ * default and maclab_autotune take several where that is faster, and the
+ * tiling reported is that of the single steps. */
 int maclab_get_tiling(maclab_t h, int out[5]);
 int maclab_set_tiling(maclab_t h, int kernel, int W, int nyb, int nzb, int pf);
 
@@ -306,7 +313,8 @@ int maclab_get_adjoint_tiling(maclab_t h, int out[3]);
  *                 steps_per_graph steps are captured once in a HIP graph
  *                 and replayed on a private stream ordered after and before
  *                 the caller's stream (not for MACLAB_S16, whose rounding is
- *                 keyed per step). Results are bitwise those of stepping each
+ *                 keyed per step). A launch takes several steps (as in
+ *                 maclab_step) unless set_tiling asked for a tiling. Results are bitwise those of stepping each
  *                 lattice with maclab_step on the fast D2Q9 kernel.
  *                 MACLAB_EINVAL if a lattice was stepped on its own.
  *  step_separate: the same n steps as one launch per lattice per step (the

@@ -138,6 +138,50 @@ hipError_t launch_step_fast2d_items(int precision, int kx, const void* src, void
                                     const int4* items, int nitems, double rho_ref, uint32_t sr_key,
                                     bool stream_stores, hipStream_t s);
 
+// Several D2Q9 steps per launch (kernels_2d_multi.hip): tiles of 64 nodes by
+// r nw rows that overlap by the steps of the launch (`steps`, at most) on each
+// side. multi2d_shapes: the best ones by a model of their time, best first.
+struct Multi2DShape {
+  int r = 1, nw = 16, steps = 0;  // steps 0: not used
+};
+constexpr int kMultiStepsMax = 12;  // steps of one launch
+constexpr int kMultiRowsMin = 4;    // rows a tile stores, at least
+bool multi2d_shape_valid(const Layout& L, const StepParams& p, const Multi2DShape& sh);
+int multi2d_tiles(const Layout& L, const StepParams& p, const Multi2DShape& sh, int halo);
+int multi2d_shapes(const Layout& L, const StepParams& p, int cus, Multi2DShape* out, int max_out);
+int multi2d_batch_shapes(const Layout* L, const StepParams* p, int count, int cus, Multi2DShape* out, int max_out);
+hipError_t launch_multi2d(const Layout& L, const void* src, void* dst, const StepParams& p, const Multi2DShape& sh,
+                          int steps, hipStream_t s);
+// The same for a batch: work items {lattice, x tile, y tile, 0} with the tiles
+// of sh.steps, advanced by `steps` <= sh.steps.
+hipError_t launch_multi2d_items(int precision, const Multi2DShape& sh, const void* src, void* dst, const Lattice2D* lat,
+                                const int4* items, int nitems, int steps, double rho_ref, uint64_t seed, uint64_t step,
+                                bool stream_stores, hipStream_t s);
+
+// Tiles of `size` nodes along an axis of n nodes that overlap by h on each
+// side. Periodic: tile k stores size - 2h nodes from k (size - 2h) and begins h
+// before them (`wraps`: one tile is the whole axis). Between fixed faces the
+// first tile begins and the last one ends at the face, without overlap there.
+struct MultiSpan {
+  int start, lo, hi;  // first node of the tile; nodes [lo, hi) that it stores
+};
+__host__ __device__ inline int multi_tiles(int n, int per, int size, int h, bool wraps) {
+  if (wraps || (!per && n <= size)) return 1;
+  const int u = size - 2 * h;
+  return per ? (n + u - 1) / u : (n - 2 * h + u - 1) / u;
+}
+__host__ __device__ inline MultiSpan multi_span(int n, int per, int size, int h, int k, bool wraps) {
+  if (wraps || (!per && n <= size)) return {0, 0, n};
+  const int u = size - 2 * h;
+  if (per) {
+    const int hi = (k + 1) * u;
+    return {k * u - h, k * u, hi < n ? hi : n};
+  }
+  const int last = k == (n - 2 * h + u - 1) / u - 1;
+  return {k * u, k == 0 ? 0 : k * u + h, last ? n : k * u + h + u};
+}
+inline int multi_tiles_x(int nx, int xper, int halo) { return multi_tiles(nx, xper, 64, halo, xper && nx == 64); }
+
 // Reverse mode (kernels_adjoint.hip). Adjoint buffers hold (Rbar, Mbar) in
 // the compute type, d + 1 planes of `plane` elements.
 int64_t adjoint_slots(const Layout& L);

@@ -23,6 +23,7 @@ struct Plan {
   int kernel = 0;
   FastShape s3;
   Fast2DShape s2;
+  Multi2DShape multi;  // kernel 3: several steps per launch (steps 0: one)
   Seg3DShape seg;      // kernel 0, FP64 D3Q19: its tiling, by the rule of seg3d_shape ...
   int seg_fixed = -1;  // ... for these face kinds (bit k: axis k is bounded)
 };
@@ -246,7 +247,9 @@ bool plan_valid(const Layout& L, const StepParams& p, const Plan& pl) {
     case 0: return true;
     case 1:
     case 2: return fast_step_supported(L, p) && pl.s3.kind == pl.kernel - 1 && fast_shape_valid(L, p, pl.s3);
-    case 3: return fast2d_supported(L, p) && fast2d_shape_valid(L, p, pl.s2);
+    case 3:
+      return fast2d_supported(L, p) && fast2d_shape_valid(L, p, pl.s2) &&
+             (pl.multi.steps == 0 || multi2d_shape_valid(L, p, pl.multi));
   }
   return false;
 }
@@ -258,7 +261,10 @@ Plan plan_default(const Layout& L, const StepParams& p, int cus) {
     pl.kernel = 1 + pl.s3.kind;
   } else if (fast2d_supported(L, p)) {
     pl.s2 = fast2d_default_shape(L, p, cus);
-    if (fast2d_shape_valid(L, p, pl.s2)) pl.kernel = 3;
+    if (fast2d_shape_valid(L, p, pl.s2)) {
+      pl.kernel = 3;
+      multi2d_shapes(L, p, cus, &pl.multi, 1);
+    }
   }
   return pl;
 }
@@ -304,6 +310,13 @@ void set_seg(const Layout& L, const StepParams& p, int cus, Plan* pl) {
   if (pl->kernel != 0 || !seg3d_supported(L) || pl->seg_fixed == fixed) return;
   pl->seg = seg3d_shape(L, p, cus);
   pl->seg_fixed = fixed;
+}
+
+// Steps of the next launch when `left` are to do, at most `most` a launch: as
+// few launches as that allows, of about equal length.
+int multi_chunk(int64_t left, int most) {
+  const int64_t launches = (left + most - 1) / most;
+  return (int)((left + launches - 1) / launches);
 }
 
 const Plan& current_plan(maclab_t h, const StepParams& p) {
@@ -439,6 +452,18 @@ int maclab_step(maclab_t h, int64_t n) {
   if (rc) return rc;
   StepParams p = make_params(h);
   const Plan pl = current_plan(h, p);
+  // Several steps per launch, but the last one alone: the other buffer then holds
+  // the state one step before, which maclab_residual compares with.
+  if (pl.kernel == 3 && pl.multi.steps > 1 && !has_derived_faces(h->fv)) {
+    while (n > 2) {
+      const int m = multi_chunk(n - 1, pl.multi.steps);
+      p.step = (uint64_t)h->steps;
+      HIP_TRY(h, launch_multi2d(h->L, h->state[h->cur], h->state[h->cur ^ 1], p, pl.multi, m, h->stream));
+      h->cur ^= 1;
+      h->steps += m;
+      n -= m;
+    }
+  }
   for (int64_t s = 0; s < n; ++s) {
     p.step = (uint64_t)h->steps;
     p.sr_key = sr_key(p.seed, p.step);
@@ -664,31 +689,55 @@ int maclab_autotune(maclab_t h, int reps, double* best_ms) {
     (void)hipEventDestroy(e0);
     return fail(h, MACLAB_EHIP, "hipEventCreate: %s", hipGetErrorString(ee));
   }
-  double best = 1e300;
-  int best_i = 0;
   hipError_t err = hipSuccess;
-  for (int i = 0; i < nc && err == hipSuccess; ++i) {
-    if ((err = launch_plan(h->L, p, cand[i], src, dst, h->stream)) != hipSuccess) break;  // warm-up
+  // ms of one launch of `launch`
+  auto timed = [&](int times, auto&& launch) -> double {
+    if ((err = launch()) != hipSuccess) return 0;  // warm-up
     double total = 0;
-    for (int r = 0; r < reps && err == hipSuccess; ++r) {
+    for (int r = 0; r < times; ++r) {
       // A time step reads a source that the step before has just written
       // with write-through stores, part of which the memory-side cache may
       // still hold, and nothing else. Launches repeated from one source would
       // find other data there (the source they read before). So before each
       // timed launch the source is copied to the spare buffer and back
       // (untimed; the same bytes, stored the way a step stores them).
-      if ((err = launch_stream_copy(src, dst, h->L.state_bytes, h->stream)) != hipSuccess) break;
-      if ((err = launch_stream_copy(dst, h->state[h->cur], h->L.state_bytes, h->stream)) != hipSuccess) break;
-      if ((err = hipEventRecord(e0, h->stream)) != hipSuccess) break;
-      if ((err = launch_plan(h->L, p, cand[i], src, dst, h->stream)) != hipSuccess) break;
-      if ((err = hipEventRecord(e1, h->stream)) != hipSuccess) break;
-      if ((err = hipEventSynchronize(e1)) != hipSuccess) break;
+      if ((err = launch_stream_copy(src, dst, h->L.state_bytes, h->stream)) != hipSuccess) return 0;
+      if ((err = launch_stream_copy(dst, h->state[h->cur], h->L.state_bytes, h->stream)) != hipSuccess) return 0;
+      if ((err = hipEventRecord(e0, h->stream)) != hipSuccess) return 0;
+      if ((err = launch()) != hipSuccess) return 0;
+      if ((err = hipEventRecord(e1, h->stream)) != hipSuccess) return 0;
+      if ((err = hipEventSynchronize(e1)) != hipSuccess) return 0;
       float ms = 0;
-      if ((err = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) break;
+      if ((err = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) return 0;
       total += ms;
     }
+    return total / times;
+  };
+  // several steps per launch first (half the repetitions: each covers several
+  // steps), so that a single step is what the spare buffer holds in the end
+  Multi2DShape best_multi;
+  double best_multi_ms = 1e300;
+  if (cand[0].kernel == 3 && !has_derived_faces(h->fv)) {
+    Multi2DShape ms[2];
+    int nm = multi2d_shapes(h->L, p, h->cus, ms, 2);
+    // up to one tile per CU a launch is mostly latency, and the events' own
+    // favours long launches: the model's choice stands
+    if (nm > 1 && multi2d_tiles(h->L, p, ms[0], ms[0].steps) <= h->cus) nm = 1;
+    for (int i = 0; i < nm; ++i) {
+      const Multi2DShape& m = ms[i];
+      const double per = timed((reps + 1) / 2, [&] { return launch_multi2d(h->L, src, dst, p, m, m.steps, h->stream); }) / m.steps;
+      if (err != hipSuccess) break;
+      if (per < best_multi_ms) {
+        best_multi_ms = per;
+        best_multi = m;
+      }
+    }
+  }
+  double best = 1e300;
+  int best_i = 0;
+  for (int i = 0; i < nc && err == hipSuccess; ++i) {
+    const double per = timed(reps, [&] { return launch_plan(h->L, p, cand[i], src, dst, h->stream); });
     if (err != hipSuccess) break;
-    const double per = total / reps;
     if (per < best) {
       best = per;
       best_i = i;
@@ -698,8 +747,9 @@ int maclab_autotune(maclab_t h, int reps, double* best_ms) {
   (void)hipEventDestroy(e1);
   if (err != hipSuccess) return fail(h, MACLAB_EHIP, "maclab_autotune: %s", hipGetErrorString(err));
   h->plan = cand[best_i];
+  h->plan.multi = best_multi_ms < best ? best_multi : Multi2DShape{};
   h->plan_set = true;
-  if (best_ms) *best_ms = best;
+  if (best_ms) *best_ms = std::min(best, best_multi_ms);
   return MACLAB_OK;
 }
 
@@ -917,6 +967,13 @@ struct maclab_batch_s {
   int up_kx = 0, up_rows = 0;
   std::vector<Lattice2D> table_host;
   std::vector<int4> items_host;
+  // several steps per launch: shape (steps 0: one), its work items (device, after `items`)
+  bool multi_auto = true;        // shape by rule (else as maclab_batch_autotune or set_tiling left it)
+  Multi2DShape multi, up_multi;
+  int4* mitems = nullptr;
+  int64_t max_mitems = 0;
+  int nmitems = 0;
+  std::vector<int4> mitems_host;
   int graph_steps = 32;          // steps per captured graph (even; 0: no graph)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -952,8 +1009,8 @@ constexpr int kBatchRowsMin = 4;
 struct BatchLayout {
   std::vector<Layout> L;
   std::vector<size_t> off;  // byte offset of each lattice in a state buffer
-  size_t states = 0, partial = 0, staging = 0, adjoint = 0, table = 0, items = 0, total = 0;
-  int64_t max_items = 0;
+  size_t states = 0, partial = 0, staging = 0, adjoint = 0, table = 0, items = 0, mitems = 0, total = 0;
+  int64_t max_items = 0, max_mitems = 0;
 };
 
 int batch_layout(const maclab_config* cfgs, int count, BatchLayout* B, std::string* why) {
@@ -990,6 +1047,9 @@ int batch_layout(const maclab_config* cfgs, int count, BatchLayout* B, std::stri
     B->staging = std::max(B->staging, B->L[i].staging_bytes);
     B->adjoint = std::max(B->adjoint, B->L[i].adjoint_bytes);
     B->max_items += ((B->L[i].nx + 63) / 64) * ((B->L[i].ny + kBatchRowsMin - 1) / kBatchRowsMin);
+    // a tile of several steps stores at least 64 - 2 kMultiStepsMax nodes by kMultiRowsMin rows
+    constexpr int64_t ux = 64 - 2 * kMultiStepsMax, uy = kMultiRowsMin;
+    B->max_mitems += ((B->L[i].nx + ux - 1) / ux) * ((B->L[i].ny + uy - 1) / uy);
   }
   if (B->max_items > (int64_t(1) << 30)) {
     *why = "too many work items";
@@ -997,7 +1057,8 @@ int batch_layout(const maclab_config* cfgs, int count, BatchLayout* B, std::stri
   }
   B->table = round_up(sizeof(Lattice2D) * (size_t)count, kAlign);
   B->items = round_up(sizeof(int4) * (size_t)B->max_items, kAlign);
-  B->total = 2 * B->states + B->partial + B->staging + B->adjoint + B->table + B->items;
+  B->mitems = round_up(sizeof(int4) * (size_t)B->max_mitems, kAlign);
+  B->total = 2 * B->states + B->partial + B->staging + B->adjoint + B->table + B->items + B->mitems;
   return MACLAB_OK;
 }
 
@@ -1064,6 +1125,43 @@ bool same_lattice(const Lattice2D& a, const Lattice2D& c) {
          a.gx == c.gx && a.gy == c.gy && a.base == c.base && a.plane == c.plane;
 }
 
+// The lattices of the batch as the shape rule sees them.
+void batch_lattices(maclab_batch_t b, std::vector<Layout>* L, std::vector<StepParams>* p) {
+  for (maclab_s* h : b->lat) {
+    L->push_back(h->L);
+    p->push_back(make_params(h));
+  }
+}
+
+bool same_shape(const Multi2DShape& a, const Multi2DShape& c) {
+  return a.r == c.r && a.nw == c.nw && a.steps == c.steps;
+}
+
+// Work items of several steps per launch: the tiles of every lattice, in the
+// order of batch_plan. Empty when the shape is unused or does not fit a lattice
+// or the workspace (the batch then takes one step per launch).
+void batch_multi_items(maclab_batch_t b, const Multi2DShape& m, std::vector<int4>* items) {
+  items->clear();
+  if (m.steps < 2) return;
+  std::vector<int> order(b->count);
+  for (int i = 0; i < b->count; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
+    return b->lat[a]->L.nx * b->lat[a]->L.ny > b->lat[c]->L.nx * b->lat[c]->L.ny;
+  });
+  for (int i : order) {
+    const Layout& L = b->lat[i]->L;
+    const StepParams p = make_params(b->lat[i]);
+    const int nxt = multi_tiles_x((int)L.nx, !p.fixed[0], m.steps);
+    const int nyt = multi_tiles((int)L.ny, !p.fixed[1], m.r * m.nw, m.steps, false);
+    if (!multi2d_shape_valid(L, p, m) || (int64_t)items->size() + (int64_t)nxt * nyt > b->max_mitems) {
+      items->clear();
+      return;
+    }
+    for (int yt = 0; yt < nyt; ++yt)
+      for (int xt = 0; xt < nxt; ++xt) items->push_back(make_int4(i, xt, yt, 0));
+  }
+}
+
 // Makes the device tables match the current tiling, faces and forces.
 int batch_sync(maclab_batch_t b) {
   std::vector<Lattice2D> table;
@@ -1072,17 +1170,31 @@ int batch_sync(maclab_batch_t b) {
   if (rc) return rc;
   bool same = b->uploaded && b->up_kx == b->kx && b->up_rows == b->rows && table.size() == b->table_host.size();
   for (size_t i = 0; same && i < table.size(); ++i) same = same_lattice(table[i], b->table_host[i]);
-  if (same) return MACLAB_OK;
+  if (same && (b->multi_auto || same_shape(b->multi, b->up_multi))) return MACLAB_OK;
+  if (b->multi_auto) {
+    std::vector<Layout> L;
+    std::vector<StepParams> p;
+    batch_lattices(b, &L, &p);
+    multi2d_batch_shapes(L.data(), p.data(), b->count, b->cus, &b->multi, 1);
+  }
+  std::vector<int4> mitems;
+  batch_multi_items(b, b->multi, &mitems);
   drop_graph(b);
   b->table_host.swap(table);
   b->items_host.swap(items);
+  b->mitems_host.swap(mitems);
   BHIP_TRY(b, hipMemcpyAsync(b->table, b->table_host.data(), sizeof(Lattice2D) * b->table_host.size(),
                              hipMemcpyHostToDevice, b->stream));
   if (!b->items_host.empty())
     BHIP_TRY(b, hipMemcpyAsync(b->items, b->items_host.data(), sizeof(int4) * b->items_host.size(),
                                hipMemcpyHostToDevice, b->stream));
+  if (!b->mitems_host.empty())
+    BHIP_TRY(b, hipMemcpyAsync(b->mitems, b->mitems_host.data(), sizeof(int4) * b->mitems_host.size(),
+                               hipMemcpyHostToDevice, b->stream));
   BHIP_TRY(b, hipStreamSynchronize(b->stream));  // the host copies may change before the next sync
   b->nitems = (int)b->items_host.size();
+  b->nmitems = (int)b->mitems_host.size();
+  b->up_multi = b->multi;
   b->uploaded = true;
   b->up_kx = b->kx;
   b->up_rows = b->rows;
@@ -1096,9 +1208,10 @@ int batch_consistent(maclab_batch_t b) {
   return MACLAB_OK;
 }
 
-void batch_advance(maclab_batch_t b, int64_t n) {
+// After `launches` launches that made n steps.
+void batch_advance(maclab_batch_t b, int64_t n, int64_t launches) {
   for (maclab_s* h : b->lat) {
-    h->cur ^= (int)(n & 1);
+    h->cur ^= (int)(launches & 1);
     h->steps += n;
   }
 }
@@ -1108,6 +1221,28 @@ int batch_launch(maclab_batch_t b, hipStream_t s, int cur, int64_t step) {
   BHIP_TRY(b, launch_step_fast2d_items(b->precision, b->kx, b->state[cur], b->state[cur ^ 1], b->table, b->items,
                                        b->nitems, b->rho_ref, key, b->state_bytes >= kStreamStoreBytes, s));
   return MACLAB_OK;
+}
+
+// Steps of a batch launch, and the launch: several at once where the batch has
+// work items for that.
+int batch_most(maclab_batch_t b) { return b->nmitems > 0 ? b->multi.steps : 1; }
+
+int batch_launch_steps(maclab_batch_t b, hipStream_t s, int cur, int64_t step, int steps) {
+  if (steps == 1) return batch_launch(b, s, cur, step);
+  BHIP_TRY(b, launch_multi2d_items(b->precision, b->multi, b->state[cur], b->state[cur ^ 1], b->table, b->mitems,
+                                   b->nmitems, steps, b->rho_ref, b->seed, (uint64_t)step,
+                                   b->state_bytes >= kStreamStoreBytes, s));
+  return MACLAB_OK;
+}
+
+// The launches of one graph of n (even) steps: an even number of them, so that
+// a replay begins and ends in buffer 0.
+std::vector<int> graph_launches(int n, int most) {
+  int k = (n + most - 1) / most;
+  k += k & 1;
+  std::vector<int> steps(k);
+  for (int i = 0; i < k; ++i) steps[i] = n * (i + 1) / k - n * i / k;
+  return steps;
 }
 
 }  // namespace
@@ -1154,6 +1289,8 @@ int maclab_batch_init(const maclab_config* cfgs, int count, void* workspace, siz
   double* gslots = (double*)(staging + B.staging);
   b->table = (Lattice2D*)(shared + B.partial + B.staging + B.adjoint);
   b->items = (int4*)((char*)b->table + B.table);
+  b->mitems = (int4*)((char*)b->items + B.items);
+  b->max_mitems = B.max_mitems;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) == hipSuccess) {
     b->device = dev;
@@ -1228,18 +1365,23 @@ int maclab_batch_step(maclab_batch_t b, int64_t n) {
   if (!rc) rc = batch_sync(b);
   if (rc) return rc;
   int64_t done = 0;
+  const int most = batch_most(b);
+  // With several steps per launch the last step is one by itself: the other buffers
+  // then hold the state one step before, which maclab_residual compares with.
+  const int64_t last = most > 1 && n > 0 ? 1 : 0;
   const bool graphs = b->graph_steps > 0 && b->precision != MACLAB_S16;  // S16 keys every step's rounding
-  if (graphs && n >= b->graph_steps + (b->lat[0]->cur & 1)) {
+  if (graphs && n - last >= b->graph_steps + (b->lat[0]->cur & 1)) {
     if (b->lat[0]->cur & 1) {  // the graph starts from buffer 0
       rc = batch_launch(b, b->stream, 1, b->lat[0]->steps);
       if (rc) return rc;
-      batch_advance(b, 1);
+      batch_advance(b, 1, 1);
       done = 1;
     }
     if (!b->exec) {
       BHIP_TRY(b, hipStreamBeginCapture(b->priv, hipStreamCaptureModeThreadLocal));
-      for (int k = 0; k < b->graph_steps; ++k) {
-        rc = batch_launch(b, b->priv, k & 1, 0);
+      int k = 0;
+      for (int m : graph_launches(b->graph_steps, most)) {
+        rc = batch_launch_steps(b, b->priv, k++ & 1, 0, m);
         if (rc) {
           hipGraph_t g = nullptr;
           (void)hipStreamEndCapture(b->priv, &g);
@@ -1250,19 +1392,21 @@ int maclab_batch_step(maclab_batch_t b, int64_t n) {
       BHIP_TRY(b, hipStreamEndCapture(b->priv, &b->graph));
       BHIP_TRY(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
     }
-    const int64_t reps = (n - done) / b->graph_steps;
+    const int64_t reps = (n - last - done) / b->graph_steps;
     BHIP_TRY(b, hipEventRecord(b->ev_in, b->stream));
     BHIP_TRY(b, hipStreamWaitEvent(b->priv, b->ev_in, 0));
     for (int64_t r = 0; r < reps; ++r) BHIP_TRY(b, hipGraphLaunch(b->exec, b->priv));
     BHIP_TRY(b, hipEventRecord(b->ev_out, b->priv));
     BHIP_TRY(b, hipStreamWaitEvent(b->stream, b->ev_out, 0));
-    batch_advance(b, reps * b->graph_steps);
+    batch_advance(b, reps * b->graph_steps, 0);  // an even number of launches each
     done += reps * b->graph_steps;
   }
-  for (; done < n; ++done) {
-    rc = batch_launch(b, b->stream, b->lat[0]->cur, b->lat[0]->steps);
+  while (done < n) {
+    const int m = n - done > 2 ? multi_chunk(n - last - done, most) : 1;
+    rc = batch_launch_steps(b, b->stream, b->lat[0]->cur, b->lat[0]->steps, m);
     if (rc) return rc;
-    batch_advance(b, 1);
+    batch_advance(b, m, 1);
+    done += m;
   }
   return MACLAB_OK;
 }
@@ -1287,7 +1431,7 @@ int maclab_batch_step_separate(maclab_batch_t b, int64_t n) {
       StepParams p = make_params(h);
       BHIP_TRY(b, launch_step_fast2d(h->L, h->state[h->cur], h->state[h->cur ^ 1], p, shapes[i], b->stream));
     }
-    batch_advance(b, 1);
+    batch_advance(b, 1, 1);
   }
   return MACLAB_OK;
 }
@@ -1311,6 +1455,8 @@ int maclab_batch_set_tiling(maclab_batch_t b, int kx, int rows) {
   if (rc) return rc;
   b->kx = kx;
   b->rows = rows;
+  b->multi_auto = false;  // the tiling asked for, step by step
+  b->multi = Multi2DShape{};
   return batch_sync(b);
 }
 
@@ -1336,54 +1482,84 @@ int maclab_batch_autotune(maclab_batch_t b, int reps, double* best_ms) {
     return bfail(b, MACLAB_EHIP, "hipEventCreate: %s", hipGetErrorString(ee));
   }
   const int kx0 = b->kx, rows0 = b->rows;
-  double best = 1e300;
+  const bool auto0 = b->multi_auto;
+  const Multi2DShape multi0 = b->multi;
+  double best = 1e300, best_multi_ms = 1e300;
   int bkx = kx0, brows = rows0;
+  Multi2DShape best_multi;
   const int cur = b->lat[0]->cur;
+  hipError_t he = hipSuccess;
+  // ms of one launch of `steps` steps with the current tables
+  auto timed = [&](int steps, int times) -> double {
+    // the spare buffer takes the output: the state is not advanced. Before
+    // each timed launch an untimed pass reads the spare buffer, so that the
+    // launch finds its source out of the caches, as a time step does.
+    rc = batch_launch_steps(b, b->stream, cur, b->lat[0]->steps, steps);
+    double total = 0;
+    for (int r = 0; !rc && he == hipSuccess && r < times; ++r) {
+      he = launch_touch(b->state[cur ^ 1], b->state_bytes, (uint32_t*)b->partials, 0x9e3779b9u, b->stream);
+      if (he == hipSuccess) he = hipEventRecord(e0, b->stream);
+      if (he == hipSuccess) rc = batch_launch_steps(b, b->stream, cur, b->lat[0]->steps, steps);
+      if (!rc && he == hipSuccess) he = hipEventRecord(e1, b->stream);
+      if (!rc && he == hipSuccess) he = hipEventSynchronize(e1);
+      float ms = 0;
+      if (!rc && he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
+      total += ms;
+    }
+    return total / times;
+  };
+  // several steps per launch first (half the repetitions), so that a single step
+  // is what the spare buffers hold in the end
+  b->multi_auto = false;
+  std::vector<Layout> L;
+  std::vector<StepParams> p;
+  batch_lattices(b, &L, &p);
+  Multi2DShape ms[2];
+  const int nm = multi2d_batch_shapes(L.data(), p.data(), b->count, b->cus, ms, 2);
+  for (int i = 0; i < nm; ++i) {
+    b->multi = ms[i];
+    if ((rc = batch_sync(b)) || he != hipSuccess) break;
+    if (batch_most(b) < 2) continue;
+    const double per = timed(b->multi.steps, (reps + 1) / 2) / b->multi.steps;
+    if (rc || he != hipSuccess) break;
+    if (per < best_multi_ms) {
+      best_multi_ms = per;
+      best_multi = b->multi;
+    }
+  }
   for (int kx : {1, 2}) {
     for (int rows : {4, 8, 16, 32, 64, 128}) {
+      if (rc || he != hipSuccess) break;
       std::vector<Lattice2D> t;
       std::vector<int4> it;
       if (batch_plan(b, kx, rows, &t, &it) != MACLAB_OK) continue;
       b->kx = kx;
       b->rows = rows;
-      rc = batch_sync(b);
-      // the spare buffer takes the output: the state is not advanced. Before
-      // each timed launch an untimed pass reads the spare buffer, so that the
-      // launch finds its source out of the caches, as a time step does.
-      if (!rc) rc = batch_launch(b, b->stream, cur, b->lat[0]->steps);
-      hipError_t he = hipSuccess;
-      double total = 0;
-      for (int r = 0; !rc && he == hipSuccess && r < reps; ++r) {
-        he = launch_touch(b->state[cur ^ 1], b->state_bytes, (uint32_t*)b->partials, 0x9e3779b9u, b->stream);
-        if (he == hipSuccess) he = hipEventRecord(e0, b->stream);
-        if (he == hipSuccess) rc = batch_launch(b, b->stream, cur, b->lat[0]->steps);
-        if (!rc && he == hipSuccess) he = hipEventRecord(e1, b->stream);
-        if (!rc && he == hipSuccess) he = hipEventSynchronize(e1);
-        float ms = 0;
-        if (!rc && he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
-        total += ms;
-      }
-      if (rc || he != hipSuccess) {
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-        if (rc) return rc;
-        return bfail(b, MACLAB_EHIP, "autotune timing: %s", hipGetErrorString(he));
-      }
-      const double per = total / reps;
-      if (per < best) {
+      if ((rc = batch_sync(b))) break;
+      const double per = timed(1, reps);
+      if (!rc && he == hipSuccess && per < best) {
         best = per;
         bkx = kx;
         brows = rows;
       }
     }
   }
+  if (rc || he != hipSuccess) {
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    b->multi_auto = auto0;
+    b->multi = multi0;
+    if (rc) return rc;
+    return bfail(b, MACLAB_EHIP, "autotune timing: %s", hipGetErrorString(he));
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   b->kx = bkx;
   b->rows = brows;
+  b->multi = best_multi_ms < best ? best_multi : Multi2DShape{};
   rc = batch_sync(b);
   if (rc) return rc;
-  if (best_ms) *best_ms = best;
+  if (best_ms) *best_ms = std::min(best, best_multi_ms);
   return MACLAB_OK;
 }
 
