@@ -22,20 +22,47 @@ namespace maclab {
 
 namespace {
 
-// One wavefront per x-row (lanes stride over the row), four rows per
-// workgroup. The step pulls: destination x gathers population a from its
-// upstream node x - c_a, so every stored population is read exactly once per
-// step (no halo re-reads; neighbouring rows share only cache lines).
-template <int Q, class T>
+// KX neighbouring values of a plane, at any element: rows are not padded, and
+// the streaming shift moves a vector by one element.
+template <class T, int KX>
+struct Vec {
+  typedef T type __attribute__((ext_vector_type(KX), aligned(sizeof(T))));
+};
+template <class T>
+struct Vec<T, 1> {
+  using type = T;
+};
+
+// One wavefront per x-row, four rows per workgroup; a lane holds KX
+// neighbouring nodes. The step pulls: destination x gathers population a from
+// its upstream node x - c_a, so every stored population is read exactly once
+// per step, in one vector load a link shifted by c_x.
+//
+// Bound: HBM (2 Q values a node). 16-byte accesses keep four times the bytes in
+// flight per load of a wavefront: D3Q19 FP32 256^3 587 us a step with one node
+// per lane, 485 with four (5.1 of the 6.75 TB/s of a copy; a copy has 2 streams,
+// this 38); 251^3, whose rows end in part of a vector, 870 and 513; D2Q9 1024^2
+// 32 and 15. Fewer workgroups on a CU change the time by under 3%.
+//
+// Stores: past the caches for a state larger than the memory-side cache (256^3
+// 485 us, 500 device-scope, 504 cached), else device-scope, which leaves the state
+// there for the next step (D2Q9 1024^2 14.9 us, 19.3 non-temporal; D3Q19 64^3
+// 8.3, 11.1).
+//
+// What a shifted vector takes from outside the row is replaced: on a periodic
+// axis by the value across the wrap. A fixed node at a row's end is stored back
+// with its own value, so that a lane's nodes are one vector store.
+template <int Q, class T, int KX, bool TAIL, bool NT>
 __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src, T* __restrict__ dst, BgkParams p) {
   using Lt = Lattice<Q>;
+  using V = typename Vec<T, KX>::type;
   const int64_t rows = p.ny * p.nz;
   // workgroups go to the eight XCDs in turn: give each XCD a contiguous
   // range of row groups, so neighbouring rows share its L2
   const int64_t nb = gridDim.x, bid = blockIdx.x;
   const int64_t per = nb >> 3, rem = nb & 7, xcd = bid & 7;
   const int64_t grp = xcd * per + (xcd < rem ? xcd : rem) + (bid >> 3);
-  const int64_t row = grp * 4 + threadIdx.y;
+  const int64_t row = grp * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.y);
   if (row >= rows) return;
   const int64_t j = row % p.ny, k = row / p.ny;
   if ((p.fixed[1] && (j == 0 || j == p.ny - 1)) || (p.fixed[2] && (k == 0 || k == p.nz - 1))) return;
@@ -44,38 +71,94 @@ __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src
   const int64_t kr[3] = {k + 1 < p.nz ? k + 1 : 0, k, k > 0 ? k - 1 : p.nz - 1};
   const T rho_ref = (T)p.rho_ref;
   const T g[3] = {(T)p.g[0], (T)p.g[1], (T)p.g[2]};
-  for (int64_t i = threadIdx.x; i < p.nx; i += 64) {
-    if (p.fixed[0] && (i == 0 || i == p.nx - 1)) continue;
-    const int64_t ir[3] = {i + 1 < p.nx ? i + 1 : 0, i, i > 0 ? i - 1 : p.nx - 1};
-    // stream: the populations arriving at x; their density deviation and
-    // momentum (Eqs. (4)-(5) in population form)
-    T f[Q];
-    T r = 0, m[3] = {0, 0, 0};
+  const int nx = (int)p.nx;
+  const int64_t own = p.nx * (j + p.ny * k);
+  for (int i = (int)threadIdx.x * KX; i < nx; i += 64 * KX) {
+    const bool lo = i == 0, hi = i + KX >= nx;  // the lane holds the row's first / last node
+    // stream: the populations arriving at the lane's nodes
+    T f[Q][KX];
+    T edge[Q] = {};  // (KX > 1) at the row's ends: what crosses a periodic wrap, or the fixed node's own value
 #pragma unroll
     for (int a = 0; a < Q; ++a) {
-      const int64_t s = ir[1 + Lt::cx[a]] + p.nx * (jr[1 + Lt::cy[a]] + p.ny * kr[1 + Lt::cz[a]]);
-      f[a] = src[(int64_t)a * p.plane + s];
+      const T* const up = src + (int64_t)a * p.plane + p.nx * (jr[1 + Lt::cy[a]] + p.ny * kr[1 + Lt::cz[a]]);
+      if constexpr (KX == 1) {
+        const int x = i - Lt::cx[a];
+        f[a][0] = up[x < 0 ? nx - 1 : (x < nx ? x : 0)];
+      } else {
+        const V v = *reinterpret_cast<const V*>(up + i - Lt::cx[a]);
+        __builtin_memcpy(f[a], &v, sizeof v);
+      }
     }
+    if constexpr (KX > 1) {
+      if (lo || hi) {
 #pragma unroll
-    for (int a = 0; a < Q; ++a) {
-      r += f[a];
-      m[0] += (T)Lt::cx[a] * f[a];
-      m[1] += (T)Lt::cy[a] * f[a];
-      m[2] += (T)Lt::cz[a] * f[a];
+        for (int a = 0; a < Q; ++a) {
+          const T* const up = src + (int64_t)a * p.plane + p.nx * (jr[1 + Lt::cy[a]] + p.ny * kr[1 + Lt::cz[a]]);
+          if (p.fixed[0])
+            edge[a] = src[(int64_t)a * p.plane + own + (lo ? 0 : nx - 1)];
+          else if (Lt::cx[a])
+            edge[a] = up[Lt::cx[a] > 0 ? nx - 1 : 0];
+        }
+      }
+      if (!p.fixed[0]) {
+#pragma unroll
+        for (int a = 0; a < Q; ++a)
+#pragma unroll
+          for (int e = 0; e < KX; ++e) {
+            if (Lt::cx[a] == 1 && e == 0) f[a][e] = lo ? edge[a] : f[a][e];
+            if (Lt::cx[a] == -1) f[a][e] = i + e == nx - 1 ? edge[a] : f[a][e];
+          }
+      }
     }
-    // collide with tau = 1: the new populations are the equilibria of the
-    // new state (the body force of test 2 enters the momentum)
-    const T rho = rho_ref + r;
-    const T inv = (T)1 / rho;
-    const T u0 = (m[0] + g[0]) * inv, u1 = (m[1] + g[1]) * inv, u2 = (m[2] + g[2]) * inv;
-    const T uu = u0 * u0 + u1 * u1 + u2 * u2;
-    const int64_t x = i + p.nx * (j + p.ny * k);
+    T r[KX], u0[KX], u1[KX], u2[KX], rho[KX], uu[KX];
+#pragma unroll
+    for (int e = 0; e < KX; ++e) {
+      // density deviation and momentum (Eqs. (4)-(5) in population form)
+      T m[3] = {0, 0, 0};
+      r[e] = 0;
+#pragma unroll
+      for (int a = 0; a < Q; ++a) {
+        r[e] += f[a][e];
+        m[0] += (T)Lt::cx[a] * f[a][e];
+        m[1] += (T)Lt::cy[a] * f[a][e];
+        m[2] += (T)Lt::cz[a] * f[a][e];
+      }
+      // collide with tau = 1: the new populations are the equilibria of the
+      // new state (the body force of test 2 enters the momentum)
+      rho[e] = rho_ref + r[e];
+      const T inv = (T)1 / rho[e];
+      u0[e] = (m[0] + g[0]) * inv, u1[e] = (m[1] + g[1]) * inv, u2[e] = (m[2] + g[2]) * inv;
+      uu[e] = u0[e] * u0[e] + u1[e] * u1[e] + u2[e] * u2[e];
+    }
+    const bool wall_lo = p.fixed[0] && lo, wall_hi = p.fixed[0] && hi;
+    if (KX == 1 && (wall_lo || wall_hi)) continue;
 #pragma unroll
     for (int a = 0; a < Q; ++a) {
-      const T cu = (T)Lt::cx[a] * u0 + (T)Lt::cy[a] * u1 + (T)Lt::cz[a] * u2;
-      const T phim1 = (T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * uu;  // phi_a - 1
-      // w_a (rho phi_a - rho_ref) = w_a (r + rho (phi_a - 1))
-      __builtin_nontemporal_store((T)Lt::wnum[a] * (r + rho * phim1) * (T)(1.0 / 36.0), &dst[(int64_t)a * p.plane + x]);
+      const int64_t at = (int64_t)a * p.plane + own + i;
+      T o[KX];
+#pragma unroll
+      for (int e = 0; e < KX; ++e) {
+        const T cu = (T)Lt::cx[a] * u0[e] + (T)Lt::cy[a] * u1[e] + (T)Lt::cz[a] * u2[e];
+        const T phim1 = (T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * uu[e];  // phi_a - 1
+        // w_a (rho phi_a - rho_ref) = w_a (r + rho (phi_a - 1))
+        o[e] = (T)Lt::wnum[a] * (r[e] + rho[e] * phim1) * (T)(1.0 / 36.0);
+        if (KX > 1 && ((wall_lo && e == 0) || (wall_hi && i + e == nx - 1))) o[e] = edge[a];
+      }
+      if (!TAIL || i + KX <= nx) {
+        V v;
+        __builtin_memcpy(&v, o, sizeof v);
+        if constexpr (NT) {
+          __builtin_nontemporal_store(v, reinterpret_cast<V*>(dst + at));
+        } else {
+          // a state of under 256 MB: a plane is within a buffer resource's range
+          buf_store<V, kStoreDevice>(v, make_buf(dst + (int64_t)a * p.plane, p.plane * (int)sizeof(T)),
+                                     (int)((own + i) * (int)sizeof(T)));
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < KX; ++e)
+          if (i + e < nx) __builtin_nontemporal_store(o[e], dst + at + e);
+      }
     }
   }
 }
@@ -153,12 +236,32 @@ __global__ void bgk_impose_kernel(T* b0, T* b1, BgkParams p, FaceValues fv, doub
   }
 }
 
-template <int Q, class T>
-hipError_t step_qt(const BgkParams& p, const void* src, void* dst, hipStream_t s) {
+template <int Q, class T, int KX, bool TAIL>
+hipError_t step_nt(const BgkParams& p, int groups, const void* src, void* dst, hipStream_t s) {
+  if ((size_t)Q * (size_t)p.plane * sizeof(T) >= kStreamStoreBytes)
+    hipLaunchKernelGGL((bgk_step_kernel<Q, T, KX, TAIL, true>), dim3((unsigned)groups), dim3(64, 4), 0, s,
+                       (const T*)src, (T*)dst, p);
+  else
+    hipLaunchKernelGGL((bgk_step_kernel<Q, T, KX, TAIL, false>), dim3((unsigned)groups), dim3(64, 4), 0, s,
+                       (const T*)src, (T*)dst, p);
+  return hipGetLastError();
+}
+
+template <int Q, class T, int KX>
+hipError_t step_kx(const BgkParams& p, const void* src, void* dst, hipStream_t s) {
   const int64_t groups = (p.ny * p.nz + 3) / 4;
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((bgk_step_kernel<Q, T>), dim3((unsigned)groups), dim3(64, 4), 0, s, (const T*)src, (T*)dst, p);
-  return hipGetLastError();
+  if (p.nx % KX) return step_nt<Q, T, KX, true>(p, (int)groups, src, dst, s);
+  return step_nt<Q, T, KX, false>(p, (int)groups, src, dst, s);
+}
+
+// Nodes per lane: a 16-byte access, as long as half of the lanes of a row have
+// one (160^3 FP32: 122 us a step against 153 with one node per lane).
+template <int Q, class T>
+hipError_t step_qt(const BgkParams& p, const void* src, void* dst, hipStream_t s) {
+  constexpr int most = 16 / (int)sizeof(T);
+  if (p.nx >= 32 * most) return step_kx<Q, T, most>(p, src, dst, s);
+  return step_kx<Q, T, 1>(p, src, dst, s);
 }
 
 }  // namespace
