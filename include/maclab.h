@@ -278,7 +278,9 @@ int maclab_adjoint_segment(maclab_t h, const void* ckpt, void* states, int64_t n
 int maclab_adjoint_result(maclab_t h, const void* state0, const void* adj0, double* dLdu0, double* dLdrho0,
                           double dLdG[3]);
 
-/* Kernel of the reverse step. kernel -1: automatic (the default); 0: the
+/* Kernel of the reverse step. kernel -1: automatic (the default; segments of
+ * D2Q9 lattices take several reverse steps per launch, with the bits of single
+ * ones); 0: the
  * general kernel (any lattice); 3: the fast D2Q9 kernel (walled x of any
  * extent, or periodic x whose extent is a multiple of kx): one
  * wavefront per (x-segment of 64*kx nodes, kx in {1,2}, band of rows),

@@ -152,6 +152,10 @@ int multi2d_shapes(const Layout& L, const StepParams& p, int cus, Multi2DShape* 
 int multi2d_batch_shapes(const Layout* L, const StepParams* p, int count, int cus, Multi2DShape* out, int max_out);
 hipError_t launch_multi2d(const Layout& L, const void* src, void* dst, const StepParams& p, const Multi2DShape& sh,
                           int steps, hipStream_t s);
+// `steps` steps from the state at src, each step's state stored: at `states`,
+// one behind the other (L.state_bytes apart).
+hipError_t launch_multi2d_trace(const Layout& L, const void* src, void* states, const StepParams& p,
+                                const Multi2DShape& sh, int steps, hipStream_t s);
 // The same for a batch: work items {lattice, x tile, y tile, 0} with the tiles
 // of sh.steps, advanced by `steps` <= sh.steps.
 hipError_t launch_multi2d_items(int precision, const Multi2DShape& sh, const void* src, void* dst, const Lattice2D* lat,
@@ -192,6 +196,14 @@ bool adjoint2d_shape_valid(const Layout& L, const StepParams& p, const Fast2DSha
 Fast2DShape adjoint2d_default_shape(const Layout& L, const StepParams& p, int cus);
 hipError_t launch_adjoint_fast2d(const Layout& L, const void* sn, const void* an1, void* an, const StepParams& p,
                                  const Fast2DShape& sh, double* gslots, hipStream_t s);
+// Several reverse steps per launch (kernels_adjoint_multi.hip), D2Q9: states
+// first, first - 1, ... of a segment (state 0 at ckpt, 1, 2, ... at states), the
+// adjoint after the first of them at an1, the one before the last written to an.
+Multi2DShape adjoint_multi_shape(const Layout& L, bool fixed_x, bool fixed_y);
+int64_t adjoint_multi_tiles(const Layout& L, bool fixed_x, bool fixed_y, const Multi2DShape& sh);
+hipError_t launch_adjoint_multi(const Layout& L, const StepParams& p, const Multi2DShape& sh, const void* ckpt,
+                                const void* states, int first, int steps, const void* an1, void* an, double* gslots,
+                                hipStream_t s);
 hipError_t launch_adjoint_seed(const Layout& L, const void* sT, const double* dLdu, void* adj, const StepParams& p,
                                double e, hipStream_t s);
 hipError_t launch_adjoint_result(const Layout& L, const void* s0, const void* adj, double* dLdu, double* dLdrho,

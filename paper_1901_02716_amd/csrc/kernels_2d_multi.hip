@@ -19,6 +19,8 @@
 //  - Between steps a value is encoded and decoded as the stored state would be
 //    (with the rounding bits of its node and step), and the sums run in the order of
 //    the single-step kernel, so T steps here have the bits of T single steps.
+//  - TRACE: every step's state is stored, one behind the other, faces included
+//    (the states a reverse sweep needs).
 #include "d2q9.h"
 #include "internal.h"
 
@@ -31,11 +33,12 @@ struct Multi2DParams {
   int nxt, nyt;          // ... or, when items == nullptr, nxt x nyt tiles of `one`
   int halo;              // overlap (>= steps)
   int steps;             // T
+  int64_t stride;        // TRACE: elements between the stored states
   double rho_ref;
   uint64_t seed, step;   // S16 rounding: key of step + s
 };
 
-template <class C, int R, int NW, bool NT>
+template <class C, int R, int NW, bool NT, bool TRACE>
 __global__ __launch_bounds__(64 * NW) void step_d2q9_multi(const typename C::elem* __restrict__ src,
                                                           typename C::elem* __restrict__ dst, Multi2DParams p) {
 #pragma clang fp contract(off)
@@ -77,12 +80,9 @@ __global__ __launch_bounds__(64 * NW) void step_d2q9_multi(const typename C::ele
   const bool active = yb < sy.hi + p.halo && (lt.yper || yb < lt.ny);
 
   const int64_t pbytes = lt.plane * EB;
-  buf_t rs[3], rd[3];
+  buf_t rs[3];
 #pragma unroll
-  for (int f = 0; f < 3; ++f) {
-    rs[f] = make_buf(src + lt.base + f * lt.plane, pbytes);
-    rd[f] = make_buf(dst + lt.base + f * lt.plane, pbytes);
-  }
+  for (int f = 0; f < 3; ++f) rs[f] = make_buf(src + lt.base + f * lt.plane, pbytes);
   E st[R][3];
 #pragma unroll
   for (int i = 0; i < R; ++i) {
@@ -96,6 +96,20 @@ __global__ __launch_bounds__(64 * NW) void step_d2q9_multi(const typename C::ele
   bool keep_y[R];
 #pragma unroll
   for (int i = 0; i < R; ++i) keep_y[i] = !lt.yper && (yr[i] == 0 || yr[i] >= lt.ny - 1);
+
+  const bool own_x = xb >= sx.lo && xb < sx.hi;
+  auto store = [&](E* to) {
+    buf_t rd[3];
+#pragma unroll
+    for (int f = 0; f < 3; ++f) rd[f] = make_buf(to + lt.base + f * lt.plane, pbytes);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const bool ok = own_x && yb + i >= sy.lo && yb + i < sy.hi && (TRACE || !keep_y[i]);
+      const int off = ok ? (int)(((int64_t)lt.pitch * (yb + i) + xb) * EB) : kOutOfRange;
+#pragma unroll
+      for (int f = 0; f < 3; ++f) buf_store<E, NT ? kStoreStream : kStoreDevice>(st[i][f], rd[f], off);
+    }
+  };
 
   const T rho_ref = (T)p.rho_ref;
   const T g36x = (T)(36.0 * lt.gx), g36y = (T)(36.0 * lt.gy);
@@ -151,15 +165,9 @@ __global__ __launch_bounds__(64 * NW) void step_d2q9_multi(const typename C::ele
         }
       }
     }
+    if constexpr (TRACE) store(dst + s * p.stride);
   }
-  const bool sxok = xb >= sx.lo && xb < sx.hi;
-#pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const bool ok = sxok && yb + i >= sy.lo && yb + i < sy.hi && !keep_y[i];
-    const int off = ok ? (int)(((int64_t)lt.pitch * (yb + i) + xb) * EB) : kOutOfRange;
-#pragma unroll
-    for (int f = 0; f < 3; ++f) buf_store<E, NT ? kStoreStream : kStoreDevice>(st[i][f], rd[f], off);
-  }
+  if constexpr (!TRACE) store(dst);
 }
 
 // ------------------------------------------------------------------ launch
@@ -249,40 +257,40 @@ int multi2d_batch_shapes(const Layout* L, const StepParams* p, int count, int cu
   });
 }
 
-template <class C, int R, int NW, bool NT>
+template <class C, int R, int NW, bool NT, bool TRACE>
 static hipError_t launch_multi(const void* src, void* dst, const Multi2DParams& mp, int tiles, hipStream_t s) {
   using E = typename C::elem;
-  hipLaunchKernelGGL((step_d2q9_multi<C, R, NW, NT>), dim3(tiles), dim3(64 * NW), 0, s, (const E*)src, (E*)dst, mp);
+  hipLaunchKernelGGL((step_d2q9_multi<C, R, NW, NT, TRACE>), dim3(tiles), dim3(64 * NW), 0, s, (const E*)src, (E*)dst,
+                     mp);
   return hipGetLastError();
 }
 
-template <class C, bool NT>
+template <class C, bool NT, bool TRACE>
 static hipError_t launch_multi_tile(const Multi2DShape& sh, const void* src, void* dst, const Multi2DParams& mp,
                                     int tiles, hipStream_t s) {
-  if (sh.r == 1 && sh.nw == 16) return launch_multi<C, 1, 16, NT>(src, dst, mp, tiles, s);
-  if (sh.r == 2 && sh.nw == 16) return launch_multi<C, 2, 16, NT>(src, dst, mp, tiles, s);
-  if (sh.r == 4 && sh.nw == 16) return launch_multi<C, 4, 16, NT>(src, dst, mp, tiles, s);
-  if (sh.r == 8 && sh.nw == 8) return launch_multi<C, 8, 8, NT>(src, dst, mp, tiles, s);
+  if (sh.r == 1 && sh.nw == 16) return launch_multi<C, 1, 16, NT, TRACE>(src, dst, mp, tiles, s);
+  if (sh.r == 2 && sh.nw == 16) return launch_multi<C, 2, 16, NT, TRACE>(src, dst, mp, tiles, s);
+  if (sh.r == 4 && sh.nw == 16) return launch_multi<C, 4, 16, NT, TRACE>(src, dst, mp, tiles, s);
+  if (sh.r == 8 && sh.nw == 8) return launch_multi<C, 8, 8, NT, TRACE>(src, dst, mp, tiles, s);
   return hipErrorInvalidValue;
 }
 
-template <bool NT>
+template <bool NT, bool TRACE>
 static hipError_t launch_multi_codec(int precision, const Multi2DShape& sh, const void* src, void* dst,
                                      const Multi2DParams& mp, int tiles, hipStream_t s) {
   switch (precision) {
-    case MACLAB_FP64: return launch_multi_tile<CodecF64, NT>(sh, src, dst, mp, tiles, s);
-    case MACLAB_FP32: return launch_multi_tile<CodecF32, NT>(sh, src, dst, mp, tiles, s);
-    case MACLAB_HILO: return launch_multi_tile<CodecHILO, NT>(sh, src, dst, mp, tiles, s);
-    case MACLAB_S16: return launch_multi_tile<CodecS16, NT>(sh, src, dst, mp, tiles, s);
+    case MACLAB_FP64: return launch_multi_tile<CodecF64, NT, TRACE>(sh, src, dst, mp, tiles, s);
+    case MACLAB_FP32: return launch_multi_tile<CodecF32, NT, TRACE>(sh, src, dst, mp, tiles, s);
+    case MACLAB_HILO: return launch_multi_tile<CodecHILO, NT, TRACE>(sh, src, dst, mp, tiles, s);
+    case MACLAB_S16: return launch_multi_tile<CodecS16, NT, TRACE>(sh, src, dst, mp, tiles, s);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_multi2d(const Layout& L, const void* src, void* dst, const StepParams& p, const Multi2DShape& sh,
-                          int steps, hipStream_t s) {
-  if (!multi2d_shape_valid(L, p, sh) || steps < 1 || steps > sh.steps) return hipErrorInvalidValue;
-  Multi2DParams mp{};
-  Lattice2D& lt = mp.one;
+// The parameters and the tile count of one lattice's launch.
+static int multi_params(const Layout& L, const StepParams& p, const Multi2DShape& sh, int steps, Multi2DParams* mp) {
+  *mp = Multi2DParams{};
+  Lattice2D& lt = mp->one;
   lt.nx = (int)L.nx;
   lt.ny = (int)L.ny;
   lt.pitch = (int)L.px;
@@ -292,18 +300,34 @@ hipError_t launch_multi2d(const Layout& L, const void* src, void* dst, const Ste
   lt.gy = p.g[1];
   lt.base = 0;
   lt.plane = L.plane;
-  mp.halo = steps;
-  mp.nxt = multi_tiles_x(lt.nx, lt.xper, steps);
-  mp.nyt = multi_tiles(lt.ny, lt.yper, sh.r * sh.nw, steps, false);
-  mp.steps = steps;
-  mp.rho_ref = p.rho_ref;
-  mp.seed = p.seed;
-  mp.step = p.step;
-  const int tiles = mp.nxt * mp.nyt;
+  mp->halo = steps;
+  mp->nxt = multi_tiles_x(lt.nx, lt.xper, steps);
+  mp->nyt = multi_tiles(lt.ny, lt.yper, sh.r * sh.nw, steps, false);
+  mp->steps = steps;
+  mp->rho_ref = p.rho_ref;
+  mp->seed = p.seed;
+  mp->step = p.step;
+  return mp->nxt * mp->nyt;
+}
+
+hipError_t launch_multi2d(const Layout& L, const void* src, void* dst, const StepParams& p, const Multi2DShape& sh,
+                          int steps, hipStream_t s) {
+  if (!multi2d_shape_valid(L, p, sh) || steps < 1 || steps > sh.steps) return hipErrorInvalidValue;
+  Multi2DParams mp;
+  const int tiles = multi_params(L, p, sh, steps, &mp);
   // stores past the caches for a state larger than the memory-side cache, as
   // in the single-step kernel
-  return L.state_bytes >= kStreamStoreBytes ? launch_multi_codec<true>(L.precision, sh, src, dst, mp, tiles, s)
-                                            : launch_multi_codec<false>(L.precision, sh, src, dst, mp, tiles, s);
+  return L.state_bytes >= kStreamStoreBytes ? launch_multi_codec<true, false>(L.precision, sh, src, dst, mp, tiles, s)
+                                            : launch_multi_codec<false, false>(L.precision, sh, src, dst, mp, tiles, s);
+}
+
+hipError_t launch_multi2d_trace(const Layout& L, const void* src, void* states, const StepParams& p,
+                                const Multi2DShape& sh, int steps, hipStream_t s) {
+  if (!multi2d_shape_valid(L, p, sh) || steps < 1 || steps > sh.steps) return hipErrorInvalidValue;
+  Multi2DParams mp;
+  const int tiles = multi_params(L, p, sh, steps, &mp);
+  mp.stride = (int64_t)(L.state_bytes / (size_t)L.bytes);
+  return launch_multi_codec<false, true>(L.precision, sh, src, states, mp, tiles, s);
 }
 
 hipError_t launch_multi2d_items(int precision, const Multi2DShape& sh, const void* src, void* dst, const Lattice2D* lat,
@@ -320,8 +344,8 @@ hipError_t launch_multi2d_items(int precision, const Multi2DShape& sh, const voi
   mp.rho_ref = rho_ref;
   mp.seed = seed;
   mp.step = step;
-  return stream_stores ? launch_multi_codec<true>(precision, sh, src, dst, mp, nitems, s)
-                       : launch_multi_codec<false>(precision, sh, src, dst, mp, nitems, s);
+  return stream_stores ? launch_multi_codec<true, false>(precision, sh, src, dst, mp, nitems, s)
+                       : launch_multi_codec<false, false>(precision, sh, src, dst, mp, nitems, s);
 }
 
 }  // namespace maclab

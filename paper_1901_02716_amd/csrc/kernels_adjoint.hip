@@ -20,6 +20,8 @@
 // The gather from the downstream nodes y + c_a needs no atomics.
 #include "internal.h"
 
+#include <algorithm>
+
 namespace maclab {
 
 namespace {
@@ -424,8 +426,14 @@ __global__ void zero_doubles_kernel(double* __restrict__ dst, int64_t count) {
 // ---------------------------------------------------------------- launchers
 int64_t adjoint_slots(const Layout& L) {
   // the generic kernel's workgroups; the fast D2Q9 kernel uses at most
-  // ceil(nx/64) x ceil(ny/4) wavefronts
-  return ((L.nx + 63) / 64) * ((L.ny + 3) / 4) * L.nz;
+  // ceil(nx/64) x ceil(ny/4) wavefronts, and that of several steps those of its
+  // tiles, for any faces
+  int64_t n = ((L.nx + 63) / 64) * ((L.ny + 3) / 4) * L.nz;
+  for (int f = 0; f < 4 && L.q == 9; ++f) {
+    const Multi2DShape sh = adjoint_multi_shape(L, f & 1, f >> 1);
+    if (sh.steps > 0) n = std::max(n, adjoint_multi_tiles(L, f & 1, f >> 1, sh) * sh.nw);
+  }
+  return n;
 }
 
 template <class F>

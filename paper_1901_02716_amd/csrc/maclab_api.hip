@@ -893,15 +893,37 @@ int maclab_adjoint_segment(maclab_t h, const void* ckpt, void* states, int64_t n
   auto slot = [&](int64_t n) -> const void* {  // state at step step_index + n
     return n == 0 ? ckpt : (const void*)((const char*)states + (size_t)(n - 1) * sb);
   };
-  // recompute the states after the checkpoint
-  for (int64_t n = 1; n < nsteps; ++n) {
+  StepParams p = make_params(h);
+  // Recompute the states after the checkpoint: several steps per launch where
+  // maclab_step takes them. With bounded faces the first one alone, since a
+  // recomputed state holds the handle's face values, not the checkpoint's.
+  const Plan pl = current_plan(h, p);
+  const bool bounded = p.fixed[0] || p.fixed[1] || p.fixed[2];
+  const bool several = pl.kernel == 3 && pl.multi.steps > 1;
+  for (int64_t n = 1; n < nsteps;) {
+    if (several && nsteps - n > 1 && (n > 1 || !bounded)) {
+      const int m = multi_chunk(nsteps - n, pl.multi.steps);
+      p.step = (uint64_t)(step_index + n - 1);
+      HIP_TRY(h, launch_multi2d_trace(h->L, slot(n - 1), (void*)slot(n), p, pl.multi, m, h->stream));
+      n += m;
+      continue;
+    }
     rc = maclab_step_external(h, slot(n - 1), (void*)slot(n), step_index + n - 1);
     if (rc) return rc;
+    ++n;
   }
   void* adj[2] = {adj_a, adj_b};
   int cur = *which;
-  const StepParams p = make_params(h);
-  for (int64_t n = nsteps - 1; n >= 0; --n) {
+  // several reverse steps per launch, whatever the length of the segment (the
+  // force derivative's sums then do not depend on it)
+  const Multi2DShape sh = h->adj_kernel == -1 ? adjoint_multi_shape(h->L, p.fixed[0], p.fixed[1]) : Multi2DShape{};
+  for (int64_t n = nsteps - 1; sh.steps > 0 && n >= 0;) {
+    const int m = multi_chunk(n + 1, sh.steps);
+    HIP_TRY(h, launch_adjoint_multi(h->L, p, sh, ckpt, states, (int)n, m, adj[cur], adj[cur ^ 1], h->gslots, h->stream));
+    n -= m;
+    cur ^= 1;
+  }
+  for (int64_t n = nsteps - 1; sh.steps == 0 && n >= 0; --n) {
     rc = adjoint_one(h, p, slot(n), adj[cur], adj[cur ^ 1]);
     if (rc) return rc;
     cur ^= 1;
