@@ -188,8 +188,8 @@ int maclab_save_state(maclab_t h, void* dst_device);
 int maclab_load_state(maclab_t h, const void* src_device);
 
 /* Kernel and tiling of the step. out[5] = {kernel, W, nyb, nzb, pf}.
- *  kernel 0: general kernel (any shape and boundaries; no tiling to set; FP64
- *    D3Q19 runs it as row segments with an LDS exchange).
+ *  kernel 0: general kernel (any shape and boundaries; no tiling to set: D3Q19
+ *    runs it as row segments that march in z).
  *  kernel 1: fast D3Q19, LDS exchange (row pitch 64, 128 or 256: x extent
  *    64, 128 or 256, or between fixed x faces an extent padded to one of
  *    them; FP32 arithmetic): one wavefront per x-row marches in z;

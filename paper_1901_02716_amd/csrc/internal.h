@@ -98,6 +98,13 @@ int fast_candidates(const Layout& L, const StepParams& p, int cus, FastShape* ou
 hipError_t launch_step_fast(const Layout& L, const void* src, void* dst, const StepParams& p, const FastShape& sh,
                             hipStream_t s);
 
+// D3Q19, any lattice (kernels_rows.hip).
+hipError_t launch_step_rows(const Layout& L, const void* src, void* dst, const StepParams& p, int cus, hipStream_t s);
+// Nodes from which the FP64 D3Q19 step is worth a march in z: below, the chain
+// of plane steps (6.5 us at 20k nodes, against 4.8) takes longer than one thread
+// per node with all its loads at once.
+constexpr int64_t kMarchNodes64 = 40960;
+
 // FP64 D3Q19 path (kernels_seg.hip), the general kernel's form for FP64: rows
 // of any width cut into segments of 64 kx nodes, workgroups of w output rows,
 // nyb x nzb of them per segment.

@@ -34,7 +34,9 @@ __device__ __forceinline__ int64_t wrap_idx(int64_t v, int64_t n) {
 }
 
 // One thread per destination node; the upstream values come through the
-// cache. Handles every shape, periodic wrap on any axis and fixed faces.
+// cache. Handles every shape, periodic wrap on any axis and fixed faces: D2Q9
+// lattices that are not the fast kernel's, and small FP64 D3Q19 lattices (larger
+// ones and the other storages march in z: kernels_seg.hip, kernels_rows.hip).
 template <int Q, class C>
 __global__ __launch_bounds__(256) void step_generic_kernel(const typename C::elem* __restrict__ src,
                                                            typename C::elem* __restrict__ dst,
@@ -346,10 +348,13 @@ hipError_t launch_step_generic(const Layout& L, const void* src, void* dst, cons
   return dispatch_codec(L.precision, [&](auto codec) {
     using C = decltype(codec);
     using E = typename C::elem;
-    if (L.q == 9)
+    if (L.q == 9) {
       hipLaunchKernelGGL((step_generic_kernel<9, C>), grid, block, 0, s, (const E*)src, (E*)dst, p);
-    else
+    } else if constexpr (sizeof(typename C::T) == 8) {
       hipLaunchKernelGGL((step_generic_kernel<19, C>), grid, block, 0, s, (const E*)src, (E*)dst, p);
+    } else {
+      return hipErrorInvalidValue;  // kernels_rows.hip
+    }
     return hipGetLastError();
   });
 }

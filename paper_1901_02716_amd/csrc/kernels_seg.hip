@@ -270,9 +270,10 @@ __global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_seg(const typename C:
 
 // ------------------------------------------------------------------ launch
 bool seg3d_supported(const Layout& L) {
-  // (The FP32-arithmetic storages keep the general kernel, whose sums run in
+  // (The FP32-arithmetic storages take the row kernel, whose sums run in
   // another order.) Three rows and planes; buffer offsets are 31-bit.
-  return L.q == 19 && L.precision == MACLAB_FP64 && L.ny >= 3 && L.nz >= 3 && L.plane * L.bytes < (int64_t(1) << 31);
+  return L.q == 19 && L.precision == MACLAB_FP64 && L.N >= kMarchNodes64 && L.ny >= 3 && L.nz >= 3 &&
+         L.plane * L.bytes < (int64_t(1) << 31);
 }
 
 // The tiling, from a model of the time: a workgroup's plane step costs each of

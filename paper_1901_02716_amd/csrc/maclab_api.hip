@@ -294,14 +294,17 @@ int plan_candidates(const Layout& L, const StepParams& p, int cus, Plan* out, in
   return n;
 }
 
-hipError_t launch_plan(const Layout& L, const StepParams& p, const Plan& pl, const void* src, void* dst,
+hipError_t launch_plan(const Layout& L, const StepParams& p, const Plan& pl, int cus, const void* src, void* dst,
                        hipStream_t s) {
   switch (pl.kernel) {
     case 1:
     case 2: return launch_step_fast(L, src, dst, p, pl.s3, s);
     case 3: return launch_step_fast2d(L, src, dst, p, pl.s2, s);
   }
-  return pl.seg_fixed >= 0 ? launch_step_seg(L, src, dst, p, pl.seg, s) : launch_step_generic(L, src, dst, p, s);
+  if (pl.seg_fixed >= 0) return launch_step_seg(L, src, dst, p, pl.seg, s);
+  if (L.q == 19 && (L.precision != MACLAB_FP64 || L.N >= kMarchNodes64))
+    return launch_step_rows(L, src, dst, p, cus, s);
+  return launch_step_generic(L, src, dst, p, s);
 }
 
 // The tiling of the FP64 D3Q19 kernel for the lattice's current faces.
@@ -469,7 +472,7 @@ int maclab_step(maclab_t h, int64_t n) {
     p.sr_key = sr_key(p.seed, p.step);
     const void* src = h->state[h->cur];
     void* dst = h->state[h->cur ^ 1];
-    HIP_TRY(h, launch_plan(h->L, p, pl, src, dst, h->stream));
+    HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, src, dst, h->stream));
     HIP_TRY(h, launch_derive_faces(h->L, dst, h->fv, h->stream));
     h->cur ^= 1;
     ++h->steps;
@@ -736,7 +739,7 @@ int maclab_autotune(maclab_t h, int reps, double* best_ms) {
   double best = 1e300;
   int best_i = 0;
   for (int i = 0; i < nc && err == hipSuccess; ++i) {
-    const double per = timed(reps, [&] { return launch_plan(h->L, p, cand[i], src, dst, h->stream); });
+    const double per = timed(reps, [&] { return launch_plan(h->L, p, cand[i], h->cus, src, dst, h->stream); });
     if (err != hipSuccess) break;
     if (per < best) {
       best = per;
@@ -771,7 +774,7 @@ int maclab_step_external(maclab_t h, const void* src, void* dst, int64_t step_in
   p.step = (uint64_t)step_index;
   p.sr_key = sr_key(p.seed, p.step);
   const Plan pl = current_plan(h, p);
-  HIP_TRY(h, launch_plan(h->L, p, pl, src, dst, h->stream));
+  HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, src, dst, h->stream));
   bool any_bounded = false;
   for (int f = 0; f < 6; ++f) any_bounded |= h->fv.kind[f] != MACLAB_BC_PERIODIC;
   if (any_bounded) HIP_TRY(h, launch_impose_bc(h->L, dst, dst, h->fv, h->cfg.rho_ref, h->e, h->stream));

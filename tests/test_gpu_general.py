@@ -1,8 +1,11 @@
-"""The D3Q19 step at the edges of the tiles of its FP64 kernel (segments of 64
-and 128 nodes, workgroups of 6 and 14 rows) against the FP64 oracle.
+"""The general D3Q19 step against the FP64 oracle at the edges of its tiles:
+the FP64 kernel (segments of 64 and 128 nodes, workgroups of 6 and 14 rows, from
+40960 nodes; fewer take one thread per node) and that of the other storages
+(segments of 62 nodes, chunks of planes).
 
-Tolerance: the FP64 bar of the other parity tests, 1e-12 relative L2 (a step
-rounds about 40 operations on values of the size of u, 1e-15 per step)."""
+Tolerances: the bars of the other parity tests, relative L2: FP64 1e-12 (a step
+rounds about 40 operations on values of the size of u, 1e-15 per step), FP32 1e-5,
+split storage 2e-3 (a few units of its resolution)."""
 import pytest
 
 import oracle
@@ -15,9 +18,36 @@ pytestmark = pytest.mark.gpu
 SIZES = [(3, 3, 3), (63, 7, 9), (64, 14, 5), (65, 15, 4), (66, 8, 5), (127, 6, 3), (128, 9, 17), (129, 20, 7),
          (130, 17, 6), (192, 5, 30), (250, 13, 8), (256, 7, 5), (258, 16, 6), (300, 29, 4)]
 
+LARGE = [(3, 120, 115), (63, 30, 23), (64, 29, 23), (65, 31, 22), (66, 28, 23), (127, 20, 17), (128, 27, 13),
+         (129, 20, 17), (130, 17, 19), (192, 15, 15), (250, 13, 13), (256, 13, 13), (258, 16, 11), (300, 29, 5)]
+ROWS = [(1, 1, 1), (2, 3, 2), (3, 3, 3), (4, 1, 9), (24, 11, 7), (61, 7, 4), (62, 5, 5), (63, 9, 4), (64, 8, 6),
+        (65, 5, 9), (124, 5, 3), (125, 6, 4), (126, 7, 3), (127, 4, 4), (187, 60, 40)]
+
+
+@pytest.mark.parametrize("precision,tol", [("fp32", 1e-5), ("hilo", 2e-3), ("s16", 2e-3)])
+@pytest.mark.parametrize("walls", ["", "xyz", "yz", "x"])
+@pytest.mark.parametrize("n", ROWS)
+def test_rows_at_segment_edges(n, walls, precision, tol):
+    if any(n["xyz".index(ax)] < 3 for ax in walls):
+        pytest.skip("a bounded axis needs three nodes")
+    case = workloads.random_field(19, n, seed=3, amp=0.03)
+    for ax in walls:
+        case.fixed[ax + "lo"] = (1.0, (0.0, 0.01, 0.0))
+        case.fixed[ax + "hi"] = (1.002, (0.02, 0.0, 0.0))
+    case.G = (0.1, 0.2, -0.1)
+    sim = Simulation(19, n, case.dx, case.nu, precision=precision, body_force=case.G, seed=2)
+    sim.set_fields(case.rho, case.u)
+    for f, (rb, ub) in case.fixed.items():
+        sim.set_bc(f, rb, ub)
+    sim.set_tiling(kernel="general")
+    sim.step(5)
+    rho, u = sim.fields()
+    orho, ou = oracle.run(to_problem(case), case.rho, case.u, 5)
+    assert rel_l2(u, ou) < tol and rel_l2(rho, orho) < tol
+
 
 @pytest.mark.parametrize("walls", ["", "xyz", "yz", "x"])
-@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("n", SIZES + LARGE)
 def test_fp64_step_at_tile_edges(n, walls):
     case = workloads.random_field(19, n, seed=3, amp=0.03)
     for ax in walls:
