@@ -52,13 +52,19 @@ inline unsigned blocks_256(int64_t count) {
 // status.
 hipError_t launch_step_generic(const Layout& L, const void* src, void* dst, const StepParams& p,
                                hipStream_t s);
-hipError_t launch_impose_bc(const Layout& L, void* buf0, void* buf1, const FaceValues& fv, double rho_ref,
-                            double e, hipStream_t s);
+// Face values into `count` buffers, stride_bytes apart.
+hipError_t launch_impose_bc(const Layout& L, void* base, int64_t stride_bytes, int count, const FaceValues& fv,
+                            double rho_ref, double e, hipStream_t s);
 // Faces with a zero normal gradient (MACLAB_BC_RHO_NEUMANN: density;
 // MACLAB_BC_PRESSURE: velocity) copy it from their nearest interior nodes in
 // `buf`; nothing is launched when no face is of those kinds.
 bool has_derived_faces(const FaceValues& fv);
 hipError_t launch_derive_faces(const Layout& L, void* buf, const FaceValues& fv, hipStream_t s);
+// All fields of all nodes, from dense FP64 arrays into both buffers / to them.
+hipError_t launch_encode_all(const Layout& L, void* b0, void* b1, const double* rho, const double* u, double rho_ref,
+                             double e, hipStream_t s);
+hipError_t launch_decode_all(const Layout& L, double* rho, double* u, const void* state, double rho_ref, double e,
+                             hipStream_t s);
 // Dense nodes first .. first+count-1 of one field plane (dense index: x
 // fastest over nx, no row padding) from / to FP64 arrays of count values.
 hipError_t launch_encode(const Layout& L, void* plane_dst, const double* src, int64_t first, int64_t count,

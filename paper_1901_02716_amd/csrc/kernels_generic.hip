@@ -86,35 +86,46 @@ __global__ __launch_bounds__(256) void step_generic_kernel(const typename C::ele
   if constexpr (D == 3) store_field<C>(dst, p.plane, 3, x, (mz + (T)(36.0 * p.g[2])) * inv, bits);
 }
 
-// Writes what each bounded face holds into both buffers: (rho_b, u_b) on a
-// fixed face, u_b on a face with a zero-gradient density, rho_b on a pressure
-// face. A node on several bounded faces belongs to the lowest-numbered one.
-// The other values of the last two kinds come from derive_faces_kernel.
+// The nodes of one face (`t` of the n x n that span it) and whether the face
+// owns the node: a node on several bounded faces belongs to the lowest-numbered.
+__device__ __forceinline__ bool face_node(const FaceValues& fv, const int64_t (&n)[3], int face, int64_t t,
+                                          int64_t (&idx)[3]) {
+  const int ax = face / 2, ab = ax == 0 ? 1 : 0, ac = ax == 2 ? 1 : 2;
+  idx[ax] = (face & 1) ? n[ax] - 1 : 0;
+  idx[ab] = t % n[ab];
+  idx[ac] = t / n[ab];
+  for (int g = 0; g < face; ++g) {
+    if (fv.kind[g] == MACLAB_BC_PERIODIC) continue;
+    if (idx[g / 2] == ((g & 1) ? n[g / 2] - 1 : 0)) return false;
+  }
+  return true;
+}
+
+// Writes what each bounded face holds into `count` buffers `stride` elements
+// apart: (rho_b, u_b) on a fixed face, u_b on a face with a zero-gradient
+// density, rho_b on a pressure face. The other values of the last two kinds
+// come from derive_faces_kernel. One thread per node of a face (blockIdx.y =
+// face): 251^3 FP64 7 us, against 107 for a pass over all nodes.
 template <class C>
-__global__ void impose_bc_kernel(typename C::elem* b0, typename C::elem* b1, int64_t nx, int64_t ny,
-                                 int64_t nz, int64_t px, int64_t plane, int d, FaceValues fv, double rho_ref,
-                                 double e) {
-  const int64_t N = nx * ny * nz;
+__global__ void impose_bc_kernel(typename C::elem* b, int64_t stride, int count, int64_t nx, int64_t ny, int64_t nz,
+                                 int64_t px, int64_t plane, int d, FaceValues fv, double rho_ref, double e) {
+  const int face = blockIdx.y;
+  const int kind = fv.kind[face];
+  if (kind == MACLAB_BC_PERIODIC) return;
   const int64_t n[3] = {nx, ny, nz};
-  for (int64_t di = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; di < N; di += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t idx[3] = {di % nx, (di / nx) % ny, di / (nx * ny)};
-    const int64_t x = stored_index(di, nx, px);
-    int face = -1;
-    for (int f = 0; f < 6 && face < 0; ++f) {
-      if (fv.kind[f] == MACLAB_BC_PERIODIC) continue;
-      const int ax = f / 2;
-      if (idx[ax] == ((f & 1) ? n[ax] - 1 : 0)) face = f;
-    }
-    if (face < 0) continue;
-    typename C::elem v[4];
-    v[0] = C::enc_nearest((typename C::T)(fv.rho[face] - rho_ref), 0);
-    for (int c = 0; c < d; ++c) v[1 + c] = C::enc_nearest((typename C::T)(fv.u[face][c] / e), 1 + c);
-    const int first = fv.kind[face] == MACLAB_BC_RHO_NEUMANN ? 1 : 0;
-    const int last = fv.kind[face] == MACLAB_BC_PRESSURE ? 0 : d;
-    for (int f = first; f <= last; ++f) {
-      b0[f * plane + x] = v[f];
-      b1[f * plane + x] = v[f];
-    }
+  const int ax = face / 2;
+  const int64_t nodes = n[ax == 0 ? 1 : 0] * n[ax == 2 ? 1 : 2];
+  typename C::elem v[4];
+  v[0] = C::enc_nearest((typename C::T)(fv.rho[face] - rho_ref), 0);
+  for (int c = 0; c < d; ++c) v[1 + c] = C::enc_nearest((typename C::T)(fv.u[face][c] / e), 1 + c);
+  const int first = kind == MACLAB_BC_RHO_NEUMANN ? 1 : 0;
+  const int last = kind == MACLAB_BC_PRESSURE ? 0 : d;
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nodes; t += (int64_t)gridDim.x * blockDim.x) {
+    int64_t idx[3];
+    if (!face_node(fv, n, face, t, idx)) continue;
+    const int64_t x = idx[0] + px * (idx[1] + ny * idx[2]);
+    for (int k = 0; k < count; ++k)
+      for (int f = first; f <= last; ++f) b[k * stride + f * plane + x] = v[f];
   }
 }
 
@@ -132,19 +143,11 @@ __global__ void derive_faces_kernel(E* buf, int64_t nx, int64_t ny, int64_t nz, 
   const int kind = fv.kind[face];
   if (kind != MACLAB_BC_RHO_NEUMANN && kind != MACLAB_BC_PRESSURE) return;
   const int64_t n[3] = {nx, ny, nz};
-  const int ax = face / 2, ab = ax == 0 ? 1 : 0, ac = ax == 2 ? 1 : 2;
-  const int64_t count = n[ab] * n[ac];
+  const int ax = face / 2;
+  const int64_t count = n[ax == 0 ? 1 : 0] * n[ax == 2 ? 1 : 2];
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count; t += (int64_t)gridDim.x * blockDim.x) {
     int64_t idx[3];
-    idx[ax] = (face & 1) ? n[ax] - 1 : 0;
-    idx[ab] = t % n[ab];
-    idx[ac] = t / n[ab];
-    bool owned = true;  // by no lower-numbered bounded face
-    for (int g = 0; g < face; ++g) {
-      if (fv.kind[g] == MACLAB_BC_PERIODIC) continue;
-      if (idx[g / 2] == ((g & 1) ? n[g / 2] - 1 : 0)) owned = false;
-    }
-    if (!owned) continue;
+    if (!face_node(fv, n, face, t, idx)) continue;
     int64_t in[3];
     for (int a = 0; a < 3; ++a) {
       in[a] = idx[a];
@@ -177,6 +180,37 @@ __global__ void decode_kernel(double* dst, const typename C::elem* __restrict__ 
                               int64_t nx, int64_t px, double offset, double mul, int field) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
     dst[i] = offset + mul * (double)C::dec(src[stored_index(first + i, nx, px)], field);
+}
+
+// All fields of all nodes at once (blockIdx.y: field), between the dense FP64
+// arrays of a caller and one state (decode) or both state buffers (encode), with
+// the arithmetic of the two kernels above: one launch for what is one launch a
+// field and a copy of the buffer otherwise, which for a small lattice is all it
+// takes.
+template <class C>
+__global__ void encode_all_kernel(typename C::elem* __restrict__ b0, typename C::elem* __restrict__ b1,
+                                  const double* __restrict__ rho, const double* __restrict__ u, int64_t N, int64_t nx,
+                                  int64_t px, int64_t plane, double rho_ref, double inv_e) {
+  const int f = blockIdx.y;
+  const double* const src = f == 0 ? rho : u + (f - 1) * N;
+  const double offset = f == 0 ? rho_ref : 0.0, mul = f == 0 ? 1.0 : inv_e;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t x = f * plane + stored_index(i, nx, px);
+    const typename C::elem v = C::enc_nearest((typename C::T)((src[i] - offset) * mul), f);
+    b0[x] = v;
+    b1[x] = v;
+  }
+}
+
+template <class C>
+__global__ void decode_all_kernel(double* __restrict__ rho, double* __restrict__ u,
+                                  const typename C::elem* __restrict__ state, int64_t N, int64_t nx, int64_t px,
+                                  int64_t plane, double rho_ref, double e) {
+  const int f = blockIdx.y;
+  double* const dst = f == 0 ? rho : u + (f - 1) * N;
+  const double offset = f == 0 ? rho_ref : 0.0, mul = f == 0 ? 1.0 : e;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x)
+    dst[i] = offset + mul * (double)C::dec(state[f * plane + stored_index(i, nx, px)], f);
 }
 
 // ------------------------------------------------------------ diagnostics
@@ -242,13 +276,18 @@ __global__ __launch_bounds__(256) void diag_final_kernel(const double* __restric
                                                          double* __restrict__ out) {
   __shared__ double red[kDiagValues][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int v = 0; v < kDiagValues; ++v) {
-    double acc = 0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+  // all values of a row at once: the loads of one value do not wait for another's
+  double acc[kDiagValues] = {};
+  for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+#pragma unroll
+    for (int v = 0; v < kDiagValues; ++v) {
       const double x = partials[(int64_t)b * kDiagValues + v];
-      acc = (v == 5) ? fmax(acc, x) : acc + x;
+      acc[v] = (v == 5) ? fmax(acc[v], x) : acc[v] + x;
     }
-    const double r = (v == 5) ? wave_max(acc) : wave_sum(acc);
+  }
+#pragma unroll
+  for (int v = 0; v < kDiagValues; ++v) {
+    const double r = (v == 5) ? wave_max(acc[v]) : wave_sum(acc[v]);
     if (lane == 0) red[v][wave] = r;
   }
   __syncthreads();
@@ -311,13 +350,17 @@ __global__ __launch_bounds__(256) void residual_final_kernel(const double* __res
                                                              double* __restrict__ out) {
   __shared__ double red[3][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int v = 0; v < 3; ++v) {
-    double acc = 0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+  double acc[3] = {};
+  for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
       const double x = partials[(int64_t)b * 4 + v];
-      acc = v < 2 ? fmax(acc, x) : acc + x;
+      acc[v] = v < 2 ? fmax(acc[v], x) : acc[v] + x;
     }
-    const double r = v < 2 ? wave_max(acc) : wave_sum(acc);
+  }
+#pragma unroll
+  for (int v = 0; v < 3; ++v) {
+    const double r = v < 2 ? wave_max(acc[v]) : wave_sum(acc[v]);
     if (lane == 0) red[v][wave] = r;
   }
   __syncthreads();
@@ -359,14 +402,44 @@ hipError_t launch_step_generic(const Layout& L, const void* src, void* dst, cons
   });
 }
 
-hipError_t launch_impose_bc(const Layout& L, void* b0, void* b1, const FaceValues& fv, double rho_ref,
-                            double e, hipStream_t s) {
-  const unsigned blocks = blocks_256(L.N);
+// Nodes of the largest face.
+static int64_t largest_face(const Layout& L) {
+  if (L.d == 2) return std::max(L.nx, L.ny);
+  return std::max(L.nx * L.ny, std::max(L.ny * L.nz, L.nx * L.nz));
+}
+
+hipError_t launch_impose_bc(const Layout& L, void* base, int64_t stride_bytes, int count, const FaceValues& fv,
+                            double rho_ref, double e, hipStream_t s) {
+  const int64_t big = largest_face(L);
+  const dim3 grid(blocks_256(big), 2 * L.d);
   return dispatch_codec(L.precision, [&](auto codec) {
     using C = decltype(codec);
     using E = typename C::elem;
-    hipLaunchKernelGGL((impose_bc_kernel<C>), dim3(blocks), dim3(256), 0, s, (E*)b0, (E*)b1, L.nx, L.ny,
-                       L.nz, L.px, L.plane, L.d, fv, rho_ref, e);
+    hipLaunchKernelGGL((impose_bc_kernel<C>), grid, dim3(256), 0, s, (E*)base, stride_bytes / (int64_t)sizeof(E), count,
+                       L.nx, L.ny, L.nz, L.px, L.plane, L.d, fv, rho_ref, e);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_encode_all(const Layout& L, void* b0, void* b1, const double* rho, const double* u, double rho_ref,
+                             double e, hipStream_t s) {
+  const dim3 grid(blocks_256(L.N), L.d + 1);
+  return dispatch_codec(L.precision, [&](auto codec) {
+    using C = decltype(codec);
+    using E = typename C::elem;
+    hipLaunchKernelGGL((encode_all_kernel<C>), grid, dim3(256), 0, s, (E*)b0, (E*)b1, rho, u, L.N, L.nx, L.px, L.plane,
+                       rho_ref, 1.0 / e);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_decode_all(const Layout& L, double* rho, double* u, const void* state, double rho_ref, double e,
+                             hipStream_t s) {
+  const dim3 grid(blocks_256(L.N), L.d + 1);
+  return dispatch_codec(L.precision, [&](auto codec) {
+    using C = decltype(codec);
+    hipLaunchKernelGGL((decode_all_kernel<C>), grid, dim3(256), 0, s, rho, u, (const typename C::elem*)state, L.N, L.nx,
+                       L.px, L.plane, rho_ref, e);
     return hipGetLastError();
   });
 }
@@ -379,7 +452,7 @@ bool has_derived_faces(const FaceValues& fv) {
 
 hipError_t launch_derive_faces(const Layout& L, void* buf, const FaceValues& fv, hipStream_t s) {
   if (!has_derived_faces(fv)) return hipSuccess;
-  const int64_t big = std::max(L.nx * L.ny, std::max(L.ny * L.nz, L.nx * L.nz));
+  const int64_t big = largest_face(L);
   const dim3 grid(blocks_256(big), 2 * L.d);
   switch (L.bytes) {
     case 2:

@@ -224,7 +224,7 @@ int check_faces(maclab_t h) {
 }
 
 int impose(maclab_t h) {
-  HIP_TRY(h, launch_impose_bc(h->L, h->state[0], h->state[1], h->fv, h->cfg.rho_ref, h->e, h->stream));
+  HIP_TRY(h, launch_impose_bc(h->L, h->state[0], h->state[1] - h->state[0], 2, h->fv, h->cfg.rho_ref, h->e, h->stream));
   HIP_TRY(h, launch_derive_faces(h->L, h->state[0], h->fv, h->stream));
   HIP_TRY(h, launch_derive_faces(h->L, h->state[1], h->fv, h->stream));
   return MACLAB_OK;
@@ -425,21 +425,21 @@ int maclab_set_fields(maclab_t h, const double* rho, const double* u, int on_dev
   if (!h) return fail(nullptr, MACLAB_EINVAL, "handle is NULL");
   if (!rho || !u) return fail(h, MACLAB_EINVAL, "rho and u must not be NULL");
   const Layout& L = h->L;
+  if (on_device) {
+    HIP_TRY(h, launch_encode_all(L, h->state[0], h->state[1], rho, u, h->cfg.rho_ref, h->e, h->stream));
+    return impose(h);
+  }
   const double offsets[4] = {h->cfg.rho_ref, 0, 0, 0};
   const double muls[4] = {1.0, 1.0 / h->e, 1.0 / h->e, 1.0 / h->e};
   for (int f = 0; f <= L.d; ++f) {
     const double* src = f == 0 ? rho : u + (size_t)(f - 1) * (size_t)L.N;
-    if (on_device) {
-      HIP_TRY(h, launch_encode(L, plane_ptr(h, h->cur, f), src, 0, L.N, offsets[f], muls[f], f, h->stream));
-    } else {
-      const int64_t chunk = (int64_t)(L.staging_bytes / sizeof(double));
-      for (int64_t off = 0; off < L.N; off += chunk) {
-        const int64_t cnt = std::min(chunk, L.N - off);
-        HIP_TRY(h, hipMemcpyAsync(h->staging, src + off, sizeof(double) * cnt, hipMemcpyHostToDevice, h->stream));
-        HIP_TRY(h, launch_encode(L, plane_ptr(h, h->cur, f), (const double*)h->staging, off,
-                                 cnt, offsets[f], muls[f], f, h->stream));
-        HIP_TRY(h, hipStreamSynchronize(h->stream));  // staging is reused
-      }
+    const int64_t chunk = (int64_t)(L.staging_bytes / sizeof(double));
+    for (int64_t off = 0; off < L.N; off += chunk) {
+      const int64_t cnt = std::min(chunk, L.N - off);
+      HIP_TRY(h, hipMemcpyAsync(h->staging, src + off, sizeof(double) * cnt, hipMemcpyHostToDevice, h->stream));
+      HIP_TRY(h, launch_encode(L, plane_ptr(h, h->cur, f), (const double*)h->staging, off,
+                               cnt, offsets[f], muls[f], f, h->stream));
+      HIP_TRY(h, hipStreamSynchronize(h->stream));  // staging is reused
     }
   }
   // the other buffer gets the same state, so fixed nodes agree in both
@@ -573,21 +573,21 @@ int maclab_get_fields(maclab_t h, double* rho, double* u, int on_device) {
   if (!h) return fail(nullptr, MACLAB_EINVAL, "handle is NULL");
   if (!rho || !u) return fail(h, MACLAB_EINVAL, "rho and u must not be NULL");
   const Layout& L = h->L;
+  if (on_device) {
+    HIP_TRY(h, launch_decode_all(L, rho, u, h->state[h->cur], h->cfg.rho_ref, h->e, h->stream));
+    return MACLAB_OK;
+  }
   const double offsets[4] = {h->cfg.rho_ref, 0, 0, 0};
   const double muls[4] = {1.0, h->e, h->e, h->e};
   for (int f = 0; f <= L.d; ++f) {
     double* dst = f == 0 ? rho : u + (size_t)(f - 1) * (size_t)L.N;
-    if (on_device) {
-      HIP_TRY(h, launch_decode(L, dst, plane_ptr(h, h->cur, f), 0, L.N, offsets[f], muls[f], f, h->stream));
-    } else {
-      const int64_t chunk = (int64_t)(L.staging_bytes / sizeof(double));
-      for (int64_t off = 0; off < L.N; off += chunk) {
-        const int64_t cnt = std::min(chunk, L.N - off);
-        HIP_TRY(h, launch_decode(L, (double*)h->staging, plane_ptr(h, h->cur, f), off, cnt,
-                                 offsets[f], muls[f], f, h->stream));
-        HIP_TRY(h, hipMemcpyAsync(dst + off, h->staging, sizeof(double) * cnt, hipMemcpyDeviceToHost, h->stream));
-        HIP_TRY(h, hipStreamSynchronize(h->stream));
-      }
+    const int64_t chunk = (int64_t)(L.staging_bytes / sizeof(double));
+    for (int64_t off = 0; off < L.N; off += chunk) {
+      const int64_t cnt = std::min(chunk, L.N - off);
+      HIP_TRY(h, launch_decode(L, (double*)h->staging, plane_ptr(h, h->cur, f), off, cnt,
+                               offsets[f], muls[f], f, h->stream));
+      HIP_TRY(h, hipMemcpyAsync(dst + off, h->staging, sizeof(double) * cnt, hipMemcpyDeviceToHost, h->stream));
+      HIP_TRY(h, hipStreamSynchronize(h->stream));
     }
   }
   return MACLAB_OK;
@@ -777,7 +777,7 @@ int maclab_step_external(maclab_t h, const void* src, void* dst, int64_t step_in
   HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, src, dst, h->stream));
   bool any_bounded = false;
   for (int f = 0; f < 6; ++f) any_bounded |= h->fv.kind[f] != MACLAB_BC_PERIODIC;
-  if (any_bounded) HIP_TRY(h, launch_impose_bc(h->L, dst, dst, h->fv, h->cfg.rho_ref, h->e, h->stream));
+  if (any_bounded) HIP_TRY(h, launch_impose_bc(h->L, dst, 0, 1, h->fv, h->cfg.rho_ref, h->e, h->stream));
   HIP_TRY(h, launch_derive_faces(h->L, dst, h->fv, h->stream));
   return MACLAB_OK;
 }
@@ -898,36 +898,47 @@ int maclab_adjoint_segment(maclab_t h, const void* ckpt, void* states, int64_t n
   };
   StepParams p = make_params(h);
   // Recompute the states after the checkpoint: several steps per launch where
-  // maclab_step takes them. With bounded faces the first one alone, since a
-  // recomputed state holds the handle's face values, not the checkpoint's.
+  // maclab_step takes them. With bounded faces the first one by itself, since a
+  // recomputed state holds the handle's face values, not the checkpoint's; the
+  // others then take them from the state before (several steps), or find them
+  // written into all states beforehand (a step leaves fixed nodes alone).
   const Plan pl = current_plan(h, p);
   const bool bounded = p.fixed[0] || p.fixed[1] || p.fixed[2];
   const bool several = pl.kernel == 3 && pl.multi.steps > 1;
-  for (int64_t n = 1; n < nsteps;) {
-    if (several && nsteps - n > 1 && (n > 1 || !bounded)) {
+  int64_t n = 1;
+  if (bounded && nsteps > 1) {
+    rc = maclab_step_external(h, slot(0), (void*)slot(1), step_index);
+    if (rc) return rc;
+    n = 2;
+    if (!several && nsteps > 2)
+      HIP_TRY(h, launch_impose_bc(h->L, (void*)slot(2), (int64_t)sb, (int)(nsteps - 2), h->fv, h->cfg.rho_ref, h->e,
+                                  h->stream));
+  }
+  while (n < nsteps) {
+    p.step = (uint64_t)(step_index + n - 1);
+    p.sr_key = sr_key(p.seed, p.step);
+    if (several) {
       const int m = multi_chunk(nsteps - n, pl.multi.steps);
-      p.step = (uint64_t)(step_index + n - 1);
       HIP_TRY(h, launch_multi2d_trace(h->L, slot(n - 1), (void*)slot(n), p, pl.multi, m, h->stream));
       n += m;
-      continue;
+    } else {
+      HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, slot(n - 1), (void*)slot(n), h->stream));
+      ++n;
     }
-    rc = maclab_step_external(h, slot(n - 1), (void*)slot(n), step_index + n - 1);
-    if (rc) return rc;
-    ++n;
   }
   void* adj[2] = {adj_a, adj_b};
   int cur = *which;
   // several reverse steps per launch, whatever the length of the segment (the
   // force derivative's sums then do not depend on it)
   const Multi2DShape sh = h->adj_kernel == -1 ? adjoint_multi_shape(h->L, p.fixed[0], p.fixed[1]) : Multi2DShape{};
-  for (int64_t n = nsteps - 1; sh.steps > 0 && n >= 0;) {
-    const int m = multi_chunk(n + 1, sh.steps);
-    HIP_TRY(h, launch_adjoint_multi(h->L, p, sh, ckpt, states, (int)n, m, adj[cur], adj[cur ^ 1], h->gslots, h->stream));
-    n -= m;
+  for (int64_t k = nsteps - 1; sh.steps > 0 && k >= 0;) {
+    const int m = multi_chunk(k + 1, sh.steps);
+    HIP_TRY(h, launch_adjoint_multi(h->L, p, sh, ckpt, states, (int)k, m, adj[cur], adj[cur ^ 1], h->gslots, h->stream));
+    k -= m;
     cur ^= 1;
   }
-  for (int64_t n = nsteps - 1; sh.steps == 0 && n >= 0; --n) {
-    rc = adjoint_one(h, p, slot(n), adj[cur], adj[cur ^ 1]);
+  for (int64_t k = nsteps - 1; sh.steps == 0 && k >= 0; --k) {
+    rc = adjoint_one(h, p, slot(k), adj[cur], adj[cur ^ 1]);
     if (rc) return rc;
     cur ^= 1;
   }
