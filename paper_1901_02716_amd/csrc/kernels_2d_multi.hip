@@ -173,7 +173,7 @@ __global__ __launch_bounds__(64 * NW) void step_d2q9_multi(const typename C::ele
 // ------------------------------------------------------------------ launch
 // Tiles: {R, NW}. One node per lane: two nodes per lane were never faster by more
 // than 5% (1024^2 FP32 2.93 us a step against 3.07) and mostly slower.
-static const int kMultiTiles[][2] = {{1, 16}, {2, 16}, {4, 16}, {8, 8}};
+static const int kMultiTiles[][2] = {{1, 16}, {2, 16}, {4, 16}, {6, 16}, {8, 8}};
 
 int multi2d_tiles(const Layout& L, const StepParams& p, const Multi2DShape& sh, int halo) {
   return multi_tiles_x((int)L.nx, !p.fixed[0], halo) * multi_tiles((int)L.ny, !p.fixed[1], sh.r * sh.nw, halo, false);
@@ -200,9 +200,16 @@ bool multi2d_shape_valid(const Layout& L, const StepParams& p, const Multi2DShap
 static double multi2d_cost(double state_bytes, int64_t tiles, const Multi2DShape& sh, int precision, int cus) {
   const int rows = sh.r * sh.nw, steps = sh.steps;
   double row = precision == MACLAB_FP32 ? 0.019 : (precision == MACLAB_FP64 ? 0.032 : 0.037);
-  // with many tiles the barriers of 8 wavefronts hold up less than those of 16
-  // (2048^2 FP32 8.5 us a step in 8x8 tiles, 9.3 in 4x16; 4096^2 33.8, 38.3)
-  if (sh.nw == 8 && tiles > 4 * (int64_t)cus) row *= 0.9;
+  // With many tiles, FP32: the barriers of 8 wavefronts hold up less than those
+  // of 16 (2048^2 8.5 us a step in 8x8 tiles, 9.3 in 4x16; 4096^2 32.7, 38.3). FP64: 8 rows a wavefront leave one workgroup to a CU, and
+  // the tallest tile of 16 wavefronts loses least to the overlap (2048^2 20.4 in
+  // 8x8, 18.0 in 6x16, 19.5 in 4x16).
+  if (tiles > 4 * (int64_t)cus) {
+    if (precision == MACLAB_FP64)
+      row *= sh.r == 6 ? 0.9 : (sh.r == 8 ? 1.05 : 1.0);
+    else if (sh.r == 8)
+      row *= 0.9;
+  }
   // tiles fill the CUs one by one; past a few each the share is continuous
   const double per_cu = tiles <= 4 * (int64_t)cus ? (double)((tiles + cus - 1) / cus) : (double)tiles / cus;
   const double step = per_cu * rows * row;
@@ -213,10 +220,13 @@ static double multi2d_cost(double state_bytes, int64_t tiles, const Multi2DShape
 // of the given tile counts (`tiles(shape)` in all); returns how many.
 template <class F>
 static int multi2d_rank(double state_bytes, int precision, int cus, Multi2DShape* out, int max_out, F&& tiles) {
-  Multi2DShape all[4];
-  double cost[4];
+  Multi2DShape all[5];
+  double cost[5];
   int n = 0;
   for (const auto& t : kMultiTiles) {
+    // 6x16 pays where a step has more work a node (1024^2 FP64 5.8 -> 5.2 us a step,
+    // split-bf16 4.6 -> 4.1, S16 5.2 -> 4.0); in FP32 it is even with 8x8 or behind
+    if (t[0] == 6 && precision == MACLAB_FP32) continue;
     Multi2DShape best, sh;
     double best_cost = 1e300;
     sh.r = t[0];
@@ -271,6 +281,7 @@ static hipError_t launch_multi_tile(const Multi2DShape& sh, const void* src, voi
   if (sh.r == 1 && sh.nw == 16) return launch_multi<C, 1, 16, NT, TRACE>(src, dst, mp, tiles, s);
   if (sh.r == 2 && sh.nw == 16) return launch_multi<C, 2, 16, NT, TRACE>(src, dst, mp, tiles, s);
   if (sh.r == 4 && sh.nw == 16) return launch_multi<C, 4, 16, NT, TRACE>(src, dst, mp, tiles, s);
+  if (sh.r == 6 && sh.nw == 16) return launch_multi<C, 6, 16, NT, TRACE>(src, dst, mp, tiles, s);
   if (sh.r == 8 && sh.nw == 8) return launch_multi<C, 8, 8, NT, TRACE>(src, dst, mp, tiles, s);
   return hipErrorInvalidValue;
 }
