@@ -194,8 +194,14 @@ __host__ __device__ inline MultiSpan multi_span(int n, int per, int size, int h,
     const int hi = (k + 1) * u;
     return {k * u - h, k * u, hi < n ? hi : n};
   }
-  const int last = k == (n - 2 * h + u - 1) / u - 1;
+  const int last = k * u + size >= n;
   return {k * u, k == 0 ? 0 : k * u + h, last ? n : k * u + h + u};
+}
+// v wrapped into 0 .. n-1. A step across an edge takes two comparisons; the
+// remainder, some forty instructions, only where a tile is wider than the axis.
+__host__ __device__ inline int wrap_near(int v, int n) {
+  v = v < 0 ? v + n : (v >= n ? v - n : v);
+  return v >= 0 && v < n ? v : (v % n + n) % n;
 }
 inline int multi_tiles_x(int nx, int xper, int halo) { return multi_tiles(nx, xper, 64, halo, xper && nx == 64); }
 

@@ -71,11 +71,11 @@ __global__ __launch_bounds__(64 * NW) void step_d2q9_multi(const typename C::ele
   const MultiSpan sy = multi_span(lt.ny, lt.yper, H, p.halo, yt, false);
   const int xb = sx.start + lane;
   const int yb = sy.start + R * wv;
-  const int xl = lt.xper ? ((xb % lt.nx) + lt.nx) % lt.nx : xb;
+  const int xl = lt.xper ? wrap_near(xb, lt.nx) : xb;
   const bool in_row = lt.xper || xb < lt.nx;
   int yr[R];  // stored rows (wrapped)
 #pragma unroll
-  for (int i = 0; i < R; ++i) yr[i] = lt.yper ? (((yb + i) % lt.ny) + lt.ny) % lt.ny : yb + i;
+  for (int i = 0; i < R; ++i) yr[i] = lt.yper ? wrap_near(yb + i, lt.ny) : yb + i;
   // rows past the last one any stored row depends on: the wavefront only joins the barriers
   const bool active = yb < sy.hi + p.halo && (lt.yper || yb < lt.ny);
 

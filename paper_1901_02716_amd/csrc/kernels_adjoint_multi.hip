@@ -75,7 +75,7 @@ __global__ __launch_bounds__(64 * NW) void adjoint_d2q9_multi(const typename C::
   const MultiSpan sx = multi_span(p.nx, p.xper, SW, p.halo, g % p.nxt, p.xper && p.nx == SW);
   const MultiSpan sy = multi_span(p.ny, p.yper, R * NW, p.halo, g / p.nxt, false);
   const int xb = sx.start + lane, yb = sy.start + R * wv;
-  const int xl = p.xper ? ((xb % p.nx) + p.nx) % p.nx : xb;
+  const int xl = p.xper ? wrap_near(xb, p.nx) : xb;
   const bool in_row = p.xper || xb < p.nx;
   const bool active = yb < sy.hi + p.halo && (p.yper || yb < p.ny);
   const bool own_x = xb >= sx.lo && xb < sx.hi;
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * NW) void adjoint_d2q9_multi(const typename C::
   bool own[R], fixed[R];
 #pragma unroll
   for (int i = 0; i < R; ++i) {
-    const int y = yb + i, yw = p.yper ? ((y % p.ny) + p.ny) % p.ny : y;
+    const int y = yb + i, yw = p.yper ? wrap_near(y, p.ny) : y;
     at[i] = active && in_row && (p.yper || y < p.ny) ? p.pitch * yw + xl : -1;
     own[i] = own_x && y >= sy.lo && y < sy.hi;
     fixed[i] = fixed_x || (!p.yper && (y == 0 || y >= p.ny - 1));
