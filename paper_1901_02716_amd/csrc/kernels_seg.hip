@@ -278,14 +278,15 @@ bool seg3d_supported(const Layout& L) {
 
 // The tiling, from a model of the time: a workgroup's plane step costs each of
 // its wavefronts a share of its CU for every node a lane holds (0.11 us per
-// wavefront and node; a fifth more with one node per lane), workgroups on a CU
-// add up, and a plane step takes at least the latency of its load, exchange and
-// barrier (0.9 us). A tile also runs the two planes beside its chunk. So the
-// rule weighs idle lanes in the last segment, halo rows and planes, and CUs
-// without a tile. Measured (us per step, kx x w): 251^3 2x6 191, 1x14 227, 1x6
+// wavefront and node; a fifth more with one node per lane, half as much again
+// for a state of 192 MB or more, which comes from memory in narrower accesses),
+// workgroups on a CU add up, and a plane step takes at least the latency of its
+// load, exchange and barrier (0.9 us). A tile also runs the two planes beside
+// its chunk. So the rule weighs idle lanes in the last segment, halo rows and
+// planes, and CUs without a tile. Measured (us per step, kx x w): 251^3 2x6 191, 1x14 227, 1x6
 // 231; 130x129x131 1x14 36.5, 1x6 43.8, 2x6 57.5 (two segments for 130 nodes);
 // 128x129x131 2x6 24.7, 1x14 35.8; 96^3 2x6 14.4, 1x14 17.6; 48x40x36 1x6 5.4,
-// 1x14 7.3.
+// 1x14 7.3; 192^3 2x6 100, 1x14 114; 256^3 2x6 216 to 221, 1x14 238 to 261.
 Seg3DShape seg3d_shape(const Layout& L, const StepParams& p, int cus) {
   const int nyo = p.fixed[1] ? (int)L.ny - 2 : (int)L.ny, nzo = p.fixed[2] ? (int)L.nz - 2 : (int)L.nz;
   const double unit = 0.11, latency = 0.9;
@@ -298,7 +299,8 @@ Seg3DShape seg3d_shape(const Layout& L, const StepParams& p, int cus) {
     if (L.px % kx || (!p.fixed[0] && L.nx % kx)) continue;
     const int nseg = (int)((L.nx + 64 * kx - 1) / (64 * kx));
     const int nyb = (nyo + w - 1) / w;
-    const double work = (w + 2) * kx * unit * (kx == 1 ? 1.2 : 1.0);
+    const double narrow = L.state_bytes < kStreamStoreBytes / 4 * 3 ? 1.2 : 1.5;
+    const double work = (w + 2) * kx * unit * (kx > 1 ? 1.0 : narrow);
     for (int nzb = 1; nzb <= nzo; ++nzb) {
       const int64_t blocks = (int64_t)nseg * nyb * nzb;
       if (nzb > 1 && blocks > 16 * (int64_t)cus) break;  // enough tiles for any balance
