@@ -73,9 +73,11 @@ __global__ __launch_bounds__(64 * kRowsWaves) void step_d3q19_rows(const typenam
   const int lane = threadIdx.x & 63;
   // XCD-aware numbering: XCD k takes a contiguous range of wavefronts, rows of a
   // segment and chunk next to each other
+  // (a grid that needs a second dimension is long enough to be taken as it comes)
   const int nblk = (int)gridDim.x, bid = (int)blockIdx.x;
   const int per = nblk >> 3, rem = nblk & 7, xcd = bid & 7;
-  const int64_t blk = (int64_t)xcd * per + (xcd < rem ? xcd : rem) + (bid >> 3);
+  const int64_t blk = gridDim.y > 1 ? (int64_t)blockIdx.y * nblk + bid
+                                    : (int64_t)xcd * per + (xcd < rem ? xcd : rem) + (bid >> 3);
   const int64_t g = blk * kRowsWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (g >= p.nwaves) return;
   const int row = (int)(g % p.nyo);
@@ -241,8 +243,9 @@ template <class C>
 static hipError_t launch_rows(const Layout& L, const void* src, void* dst, const RowsParams& rp, hipStream_t s) {
   using E = typename C::elem;
   const int64_t blocks = (rp.nwaves + kRowsWaves - 1) / kRowsWaves;
-  if (blocks > 0x7fffffff / (64 * kRowsWaves)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), block(64 * kRowsWaves);
+  constexpr int64_t kRow = int64_t(1) << 22;  // workgroups in x: under 2^32 work-items
+  const int64_t ny = (blocks + kRow - 1) / kRow;
+  const dim3 grid((unsigned)(ny > 1 ? kRow : blocks), (unsigned)ny), block(64 * kRowsWaves);
   // Stores past the caches for a state larger than the memory-side cache
   // (301x256^2 FP32: 232 us a step, 248 device-scope, 240 cached), else
   // device-scope (300x67x93 FP32: 18.7, 24.3 non-temporal, 20.6 cached).
