@@ -456,8 +456,10 @@ int maclab_step(maclab_t h, int64_t n) {
   StepParams p = make_params(h);
   const Plan pl = current_plan(h, p);
   // Several steps per launch, but the last one alone: the other buffer then holds
-  // the state one step before, which maclab_residual compares with.
-  if (pl.kernel == 3 && pl.multi.steps > 1 && !has_derived_faces(h->fv)) {
+  // the state one step before, which maclab_residual compares with. (A lattice of
+  // a batch goes step by step: all of them must be in the same buffer after the
+  // same number of steps.)
+  if (pl.kernel == 3 && pl.multi.steps > 1 && !h->view && !has_derived_faces(h->fv)) {
     while (n > 2) {
       const int m = multi_chunk(n - 1, pl.multi.steps);
       p.step = (uint64_t)h->steps;

@@ -76,3 +76,25 @@ def test_batch_steps_per_launch_do_not_change_bits(precision):
     b.step(40)
     for i in range(len(sizes)):
         assert torch.equal(a[i].save_state(), b[i].save_state()), i
+
+
+def test_lattices_of_a_batch_stepped_alike_go_on_together():
+    """Lattices that were each stepped on their own by the same number of steps
+    are in step: the batch takes them further."""
+    sizes = [(20, 30), (200, 200), (64, 64)]
+
+    def make():
+        b = Batch([(n, 0.1, 0.05, (0.1, -0.05)) for n in sizes], precision="fp32")
+        for i, (nx, ny) in enumerate(sizes):
+            case = workloads.random_field(9, (nx, ny, 1), seed=i, amp=0.03)
+            b[i].set_fields(case.rho, case.u)
+        return b
+
+    a, b = make(), make()
+    for i in range(len(sizes)):
+        a[i].step(16)
+    b.step(16)
+    a.step(5)
+    b.step(5)
+    for i in range(len(sizes)):
+        assert torch.equal(a[i].save_state(), b[i].save_state())
