@@ -6,11 +6,13 @@ the FP64 kernel (segments of 64 and 128 nodes, workgroups of 6 and 14 rows, from
 Tolerances: the bars of the other parity tests, relative L2: FP64 1e-12 (a step
 rounds about 40 operations on values of the size of u, 1e-15 per step), FP32 1e-5,
 split storage 2e-3 (a few units of its resolution)."""
+import numpy as np
 import pytest
+import torch
 
 import oracle
 from conftest import rel_l2, to_problem
-from paper_1901_02716_amd import Simulation, workloads
+from paper_1901_02716_amd import Simulation, _lib, workloads
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +75,27 @@ def test_fp64_step_at_tile_edges(n, walls):
         rho, u = sim.fields()
         orho, ou = oracle.run(to_problem(case), case.rho, case.u, 3)
         assert rel_l2(u, ou) < 1e-12 and rel_l2(rho, orho) < 1e-12
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "hilo", "s16"])
+@pytest.mark.parametrize(
+    "n", [(3, 5), (2, 3), (64, 64), (1023, 4), (1024, 3), (1025, 7), (1030, 9), (7, 300), (5, 4, 3), (61, 17, 9),
+          (100, 9, 8), (250, 6, 5), (210, 205, 200), (209, 205, 201)])
+def test_fields_on_the_device_are_those_on_the_host(n, precision):
+    """Reading the fields in one launch (pairs of nodes or single ones, arrays past
+    the caches or not) gives the bits of reading them a field at a time."""
+    lattice = 9 if len(n) == 2 else 19
+    sim = Simulation(lattice, n, 0.1, 0.05, precision=precision)
+    case = workloads.random_field(lattice, tuple(n) + (1,) * (3 - len(n)), seed=3, amp=0.03)
+    sim.set_fields(case.rho, case.u)
+    rho, u = sim.fields()
+    r, v = sim.fields(on_device=True)
+    assert np.array_equal(r.cpu().numpy(), rho) and np.array_equal(v.cpu().numpy(), u)
+    if sim.N > 1 << 20:
+        return
+    # arrays that are not aligned for pairs
+    N = rho.size
+    flat = torch.empty((sim.d + 1) * N + 3, dtype=torch.float64, device=sim.device)
+    r, v = flat[1 : 1 + N], flat[2 + N : 2 + N + sim.d * N]
+    _lib.check(sim.lib.maclab_get_fields(sim.h, r.data_ptr(), v.data_ptr(), 1), sim.h)
+    assert np.array_equal(r.cpu().numpy(), rho.ravel()) and np.array_equal(v.cpu().numpy(), u.ravel())
