@@ -308,16 +308,18 @@ int maclab_get_adjoint_tiling(maclab_t h, int out[3]);
  *                 reverse mode returns MACLAB_EUNSUPPORTED. Those calls share
  *                 the batch's scratch, so they must not overlap in time.
  *  step:          n steps of every lattice (Eqs. (4)-(5) with each
- *                 lattice's faces and force): one launch per step over a
- *                 table of work items {lattice, x-segment of 64*kx nodes,
- *                 band of `rows` rows}: lattices largest first, the items
- *                 of one lattice in row order. Runs of
- *                 steps_per_graph steps are captured once in a HIP graph
- *                 and replayed on a private stream ordered after and before
- *                 the caller's stream (not for MACLAB_S16, whose rounding is
- *                 keyed per step). A launch takes several steps (as in
- *                 maclab_step) unless set_tiling asked for a tiling. Results are bitwise those of stepping each
- *                 lattice with maclab_step on the fast D2Q9 kernel.
+ *                 lattice's faces and force). A launch covers all lattices
+ *                 through a table of work items, lattices largest first,
+ *                 the items of one lattice in row order. It takes several
+ *                 steps on tiles (as in maclab_step), or, if set_tiling asked
+ *                 for a tiling and for the steps left over, one step on items
+ *                 {lattice, x-segment of 64*kx nodes, band of `rows` rows}.
+ *                 Runs of steps_per_graph steps are captured once in a HIP
+ *                 graph and replayed on a private stream ordered after and
+ *                 before the caller's stream (not for MACLAB_S16, whose
+ *                 rounding is keyed per step). Results are bitwise those of
+ *                 stepping each lattice with maclab_step on the fast D2Q9
+ *                 kernels.
  *                 MACLAB_EINVAL if a lattice was stepped on its own.
  *  step_separate: the same n steps as one launch per lattice per step (the
  *                 schedule a loop over single lattices would use).

@@ -979,9 +979,10 @@ const char* maclab_last_error(maclab_t h) { return h ? h->err.c_str() : g_err.c_
 }  // extern "C"
 
 // ===================================================================== batch
-// Many D2Q9 lattices in one state allocation, advanced by one launch per step
-// over a table of work items (lattice, x-segment, band of rows); a run of
-// steps is captured once in a HIP graph and replayed.
+// Many D2Q9 lattices in one state allocation, advanced together by launches
+// over a table of work items (tiles for several steps per launch; {lattice,
+// x-segment, band of rows} for one); a run of steps is captured once in a HIP
+// graph and replayed.
 
 struct maclab_batch_s {
   int count = 0;

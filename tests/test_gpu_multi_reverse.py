@@ -3,9 +3,9 @@ asked for by set_adjoint_tiling, itself checked against the oracle elsewhere), a
 and beside the edges of the tiles.
 
 The velocity gradient has the same bits. The force gradient sums the same FP64
-terms in another order: at most N T terms, each rounded once, so 1e-12 of the sum
-of their sizes covers every size here (N T 2^-53 < 1e-9 would not; the pairwise
-sums of lanes and slots keep it near 1e-15)."""
+terms in another order. Lanes and slots are summed in pairs, and a slot's chain is a
+few thousand additions at most (rows of a tile times steps): its rounding is under
+1e4 x 2^-53, so 1e-12 of the sum of the terms' sizes covers every size here."""
 import numpy as np
 import pytest
 import torch
