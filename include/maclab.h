@@ -130,7 +130,10 @@ int maclab_set_fields(maclab_t h, const double* rho, const double* u, int on_dev
  * D2Q9 lattices with periodic and fixed faces take several steps per launch
  * (a tile of the lattice is advanced in registers), with the bits of single
  * steps; the last step of a call is a launch of its own, so that the other
- * buffer holds the state one step before (maclab_residual).
+ * buffer holds the state one step before (maclab_residual). However the steps
+ * are launched, an even n ends in the buffer it began in, so a call with an even
+ * n that was captured in a graph of the caller's advances the state by n steps
+ * with every replay (not for MACLAB_S16, whose rounding is keyed per step).
  * Returns MACLAB_EINVAL if the face kinds of an axis differ. */
 int maclab_step(maclab_t h, int64_t n);
 

@@ -322,6 +322,15 @@ int multi_chunk(int64_t left, int most) {
   return (int)((left + launches - 1) / launches);
 }
 
+// Launches of a call of n steps ahead of its last step, at most `most` steps each:
+// as few as possible, but so many that the buffers alternate as with single steps.
+// An even n then ends in the buffer it began in, so that a caller's captured call
+// can be replayed.
+int64_t multi_launches(int64_t n, int most) {
+  const int64_t k = (n - 1 + most - 1) / most;
+  return k + ((k + 1 - n) & 1);  // (k + 1 <= n - 1 here: k = n - 1 has the parity)
+}
+
 const Plan& current_plan(maclab_t h, const StepParams& p) {
   if (!(h->plan_set && plan_valid(h->L, p, h->plan))) {
     const Plan pl = plan_default(h->L, p, h->cus);
@@ -457,27 +466,23 @@ int maclab_step(maclab_t h, int64_t n) {
   const Plan pl = current_plan(h, p);
   // Several steps per launch, but the last one alone: the other buffer then holds
   // the state one step before, which maclab_residual compares with. (A lattice of
-  // a batch goes step by step: all of them must be in the same buffer after the
-  // same number of steps.)
-  if (pl.kernel == 3 && pl.multi.steps > 1 && !h->view && !has_derived_faces(h->fv)) {
-    while (n > 2) {
-      const int m = multi_chunk(n - 1, pl.multi.steps);
-      p.step = (uint64_t)h->steps;
-      HIP_TRY(h, launch_multi2d(h->L, h->state[h->cur], h->state[h->cur ^ 1], p, pl.multi, m, h->stream));
-      h->cur ^= 1;
-      h->steps += m;
-      n -= m;
-    }
-  }
-  for (int64_t s = 0; s < n; ++s) {
+  // a batch goes step by step.)
+  const bool several = pl.kernel == 3 && pl.multi.steps > 1 && !h->view && !has_derived_faces(h->fv);
+  for (int64_t k = several ? multi_launches(n, pl.multi.steps) : 0; n > 0; --k) {
+    const int m = several && k > 0 ? (int)((n - 1 + k - 1) / k) : 1;
     p.step = (uint64_t)h->steps;
     p.sr_key = sr_key(p.seed, p.step);
     const void* src = h->state[h->cur];
     void* dst = h->state[h->cur ^ 1];
-    HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, src, dst, h->stream));
-    HIP_TRY(h, launch_derive_faces(h->L, dst, h->fv, h->stream));
+    if (m > 1) {
+      HIP_TRY(h, launch_multi2d(h->L, src, dst, p, pl.multi, m, h->stream));
+    } else {
+      HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, src, dst, h->stream));
+      HIP_TRY(h, launch_derive_faces(h->L, dst, h->fv, h->stream));
+    }
     h->cur ^= 1;
-    ++h->steps;
+    h->steps += m;
+    n -= m;
   }
   return MACLAB_OK;
 }
@@ -1440,8 +1445,8 @@ int maclab_batch_step(maclab_batch_t b, int64_t n) {
     batch_advance(b, reps * b->graph_steps, 0);  // an even number of launches each
     done += reps * b->graph_steps;
   }
-  while (done < n) {
-    const int m = n - done > 2 ? multi_chunk(n - last - done, most) : 1;
+  for (int64_t k = most > 1 ? multi_launches(n - done, most) : 0; done < n; --k) {
+    const int m = most > 1 && k > 0 ? (int)((n - 1 - done + k - 1) / k) : 1;
     rc = batch_launch_steps(b, b->stream, b->lat[0]->cur, b->lat[0]->steps, m);
     if (rc) return rc;
     batch_advance(b, m, 1);
