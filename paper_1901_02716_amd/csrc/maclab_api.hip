@@ -1214,7 +1214,7 @@ int batch_sync(maclab_batch_t b) {
   if (rc) return rc;
   bool same = b->uploaded && b->up_kx == b->kx && b->up_rows == b->rows && table.size() == b->table_host.size();
   for (size_t i = 0; same && i < table.size(); ++i) same = same_lattice(table[i], b->table_host[i]);
-  if (same && (b->multi_auto || same_shape(b->multi, b->up_multi))) return MACLAB_OK;
+  if (same && same_shape(b->multi, b->up_multi)) return MACLAB_OK;
   if (b->multi_auto) {
     std::vector<Layout> L;
     std::vector<StepParams> p;
@@ -1224,6 +1224,7 @@ int batch_sync(maclab_batch_t b) {
   std::vector<int4> mitems;
   batch_multi_items(b, b->multi, &mitems);
   drop_graph(b);
+  b->uploaded = false;  // until all tables are
   b->table_host.swap(table);
   b->items_host.swap(items);
   b->mitems_host.swap(mitems);
@@ -1591,8 +1592,11 @@ int maclab_batch_autotune(maclab_batch_t b, int reps, double* best_ms) {
   if (rc || he != hipSuccess) {
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    b->kx = kx0;
+    b->rows = rows0;
     b->multi_auto = auto0;
     b->multi = multi0;
+    b->uploaded = false;  // the device tables are a candidate's
     if (rc) return rc;
     return bfail(b, MACLAB_EHIP, "autotune timing: %s", hipGetErrorString(he));
   }

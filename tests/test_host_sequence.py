@@ -32,3 +32,40 @@ for precision in range(4):
         assert (now == at) == (steps % 2 == 0), (precision, steps)
         at = now
 """)
+
+
+def test_a_batch_goes_on_as_before_after_its_autotuner_failed(tmp_path):
+    """An error at any of the autotuner's timings leaves the tiling, the shape of
+    several steps and the tables that belong to them as they were."""
+    standin.run(tmp_path, """
+r = standin.load()
+sizes = [(64, 64), (131, 77), (300, 200), (512, 512)]
+def launched(b):
+    out = []
+    for steps in (1, 40, 45):
+        rc, log = r.launches(r.lib.maclab_batch_step, b, steps)
+        assert rc == 0
+        out += [e[:3] for e in log]
+    return out
+for before in (None, 0, "tiling"):  # the first call that needs tables; after steps; after a tiling was set
+    def make():
+        b = r.batch(sizes, r.m.FP32)
+        assert r.lib.maclab_batch_set_graph(b, 0) == 0
+        if before == 0:
+            assert r.lib.maclab_batch_step(b, 3) == 0
+        if before == "tiling":
+            assert r.lib.maclab_batch_set_tiling(b, 1, 16) == 0
+        return b
+    want = launched(make())
+    failed = 0
+    for at in range(40):
+        b = make()
+        r.fail_event.value = at
+        rc = r.lib.maclab_batch_autotune(b, 1, None)
+        r.fail_event.value = -1
+        if rc == 0:
+            break
+        failed += 1
+        assert launched(b) == want, (before, at)
+    assert failed == 8  # two shapes of several steps, six heights of a band
+""")
