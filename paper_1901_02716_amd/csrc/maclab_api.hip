@@ -331,6 +331,10 @@ int64_t multi_launches(int64_t n, int most) {
   return k + ((k + 1 - n) & 1);  // (k + 1 <= n - 1 here: k = n - 1 has the parity)
 }
 
+// Whether the plan's several steps per launch are taken: a lattice of a batch goes
+// step by step, derived faces change after every step.
+bool takes_several(maclab_t h) { return !h->view && !has_derived_faces(h->fv); }
+
 const Plan& current_plan(maclab_t h, const StepParams& p) {
   if (!(h->plan_set && plan_valid(h->L, p, h->plan))) {
     const Plan pl = plan_default(h->L, p, h->cus);
@@ -465,9 +469,8 @@ int maclab_step(maclab_t h, int64_t n) {
   StepParams p = make_params(h);
   const Plan pl = current_plan(h, p);
   // Several steps per launch, but the last one alone: the other buffer then holds
-  // the state one step before, which maclab_residual compares with. (A lattice of
-  // a batch goes step by step.)
-  const bool several = pl.kernel == 3 && pl.multi.steps > 1 && !h->view && !has_derived_faces(h->fv);
+  // the state one step before, which maclab_residual compares with.
+  const bool several = pl.kernel == 3 && pl.multi.steps > 1 && takes_several(h);
   for (int64_t k = several ? multi_launches(n, pl.multi.steps) : 0; n > 0; --k) {
     const int m = several && k > 0 ? (int)((n - 1 + k - 1) / k) : 1;
     p.step = (uint64_t)h->steps;
@@ -727,7 +730,7 @@ int maclab_autotune(maclab_t h, int reps, double* best_ms) {
   // steps), so that a single step is what the spare buffer holds in the end
   Multi2DShape best_multi;
   double best_multi_ms = 1e300;
-  if (cand[0].kernel == 3 && !has_derived_faces(h->fv)) {
+  if (cand[0].kernel == 3 && takes_several(h)) {
     Multi2DShape ms[2];
     int nm = multi2d_shapes(h->L, p, h->cus, ms, 2);
     // up to one tile per CU a launch is mostly latency, and the events' own

@@ -69,3 +69,23 @@ for before in (None, 0, "tiling"):  # the first call that needs tables; after st
         assert launched(b) == want, (before, at)
     assert failed == 8  # two shapes of several steps, six heights of a band
 """)
+
+
+def test_a_lattice_of_a_batch_is_tuned_for_the_steps_it_takes(tmp_path):
+    """Stepped on its own it goes step by step, so its autotuner times and reports
+    single steps; so does a lattice with derived faces."""
+    standin.run(tmp_path, """
+import ctypes
+r = standin.load()
+u = (ctypes.c_double * 3)()
+view = ctypes.c_void_p(r.lib.maclab_batch_lattice(r.batch([(300, 200), (64, 64)], r.m.FP32), 0))
+derived = r.handle(9, (300, 200), r.m.FP32, "xy")
+assert r.lib.maclab_set_bc(derived, r.m.YHI, r.m.RHO_NEUMANN, 1.0, u) == 0
+for h, single in ((view, True), (derived, True), (r.handle(9, (300, 200), r.m.FP32, "xy"), False)):
+    best = ctypes.c_double()
+    rc, log = r.launches(r.lib.maclab_autotune, h, 2, ctypes.byref(best))
+    assert rc == 0 and single == (not any("multi" in e[0] for e in log))
+    assert single == (best.value == 1.0), best.value  # every timed launch takes 1 ms
+    rc, log = r.launches(r.lib.maclab_step, h, 20)
+    assert rc == 0 and single == (not any("multi" in e[0] for e in log))
+""")
