@@ -582,10 +582,14 @@ FastShape fast_default_shape(const Layout& L, const StepParams& p, int cus) {
   output_ranges(L, p, &nyo, &nzo);
   FastShape sh;
   sh.W = 8;
-  // Two planes loaded ahead where it is built (unpadded rows): 64^3 split-bf16
-  // 6.4 -> 5.9 us a step, 256^3 S16 84.1 -> 80.7, 64x256x200 S16 23.2 -> 18.9;
-  // 256x128x128 FP32 26.0 -> 26.6 is the largest loss.
-  sh.pf = L.px == L.nx ? 2 : 1;
+  // Two planes loaded ahead where that is built (unpadded rows) and pays: us a step
+  // at one and at two planes, 64^3 FP32 6.24, 5.74, split-bf16 6.17, 5.91, S16
+  // 5.94, 5.40; 128^3 FP32 16.6, 15.4, split-bf16 16.6, 15.9; 256^3 S16 83.7, 80.7,
+  // 256x200x100 split-bf16 32.4, 32.3. One plane for S16 rows of 128 nodes (128^3
+  // 14.70, 14.97; 128x64x48 7.09, 7.20) and FP32 rows of 256 (256^3 92.8, 93.4;
+  // 256x128x128 23.55, 23.78; 256x30x20 7.99, 8.12; 256x64x64 would gain, 11.8, 11.0).
+  const bool one = (L.precision == MACLAB_S16 && L.nx == 128) || (L.precision == MACLAB_FP32 && L.nx == 256);
+  sh.pf = L.px == L.nx && !one ? 2 : 1;
   sh.nyb = (nyo + sh.W - 1) / sh.W;
   sh.nzb = cus / sh.nyb;
   if (sh.nzb < 1) sh.nzb = 1;

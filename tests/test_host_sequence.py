@@ -89,3 +89,18 @@ for h, single in ((view, True), (derived, True), (r.handle(9, (300, 200), r.m.FP
     rc, log = r.launches(r.lib.maclab_step, h, 20)
     assert rc == 0 and single == (not any("multi" in e[0] for e in log))
 """)
+
+
+def test_the_default_d3q19_tiling_loads_two_planes_ahead_only_where_that_was_faster(tmp_path):
+    standin.run(tmp_path, """
+import ctypes
+r = standin.load()
+out = (ctypes.c_int * 5)()
+planes = {(n, p): 2 for n in (64, 128, 256) for p in (r.m.FP32, r.m.HILO, r.m.S16)}
+planes[128, r.m.S16] = planes[256, r.m.FP32] = 1  # measured slower with two
+planes.update({(251, p): 1 for p in (r.m.FP32, r.m.HILO, r.m.S16)})  # padded rows: not built
+for (nx, p), want in planes.items():
+    for n in ((nx, 128, 128), (nx, 30, 20)):
+        h = r.handle(19, n, p, "xyz")
+        assert r.lib.maclab_get_tiling(h, out) == 0 and out[0] == 1 and out[4] == want, (n, p, list(out))
+""")
