@@ -104,8 +104,12 @@ int fast_candidates(const Layout& L, const StepParams& p, int cus, FastShape* ou
 hipError_t launch_step_fast(const Layout& L, const void* src, void* dst, const StepParams& p, const FastShape& sh,
                             hipStream_t s);
 
-// D3Q19, any lattice (kernels_rows.hip).
-hipError_t launch_step_rows(const Layout& L, const void* src, void* dst, const StepParams& p, int cus, hipStream_t s);
+// D3Q19, any lattice (kernels_rows.hip), in nzb chunks of planes; rows_chunks: the
+// chunks for a lattice and its faces. rows_march: whether the general kernel takes this
+// form (where the FP64 path below does not apply).
+hipError_t launch_step_rows(const Layout& L, const void* src, void* dst, const StepParams& p, int nzb, hipStream_t s);
+int rows_chunks(const Layout& L, const StepParams& p, int cus);
+bool rows_march(const Layout& L);
 // Nodes from which the FP64 D3Q19 step is worth a march in z: below, the chain
 // of plane steps (6.5 us at 20k nodes, against 4.8) takes longer than one thread
 // per node with all its loads at once.

@@ -256,7 +256,35 @@ static hipError_t launch_rows(const Layout& L, const void* src, void* dst, const
   return hipGetLastError();
 }
 
-hipError_t launch_step_rows(const Layout& L, const void* src, void* dst, const StepParams& p, int cus,
+bool rows_march(const Layout& L) { return L.q == 19 && (L.precision != MACLAB_FP64 || L.N >= kMarchNodes64); }
+
+static int64_t row_segments(const Layout& L, const StepParams& p) {
+  return p.fixed[0] ? (L.nx - 2 + 61) / 62 : (L.nx + 61) / 62;
+}
+
+// Chunks of planes, by a model of the time: a plane step takes a wavefront about
+// 1 us (its loads and chain) and a SIMD 0.4 us for each of its wavefronts, and
+// a chunk also runs the two planes beside it. Up to eight wavefronts a SIMD
+// the last, nearly empty round counts in full.
+int rows_chunks(const Layout& L, const StepParams& p, int cus) {
+  const int64_t rows = row_segments(L, p) * (p.fixed[1] ? L.ny - 2 : L.ny), nzo = p.fixed[2] ? L.nz - 2 : L.nz;
+  if (rows < 1) return 1;  // (such faces are refused before a launch)
+  int64_t nzb = 1;
+  double best = 1e300;
+  for (int64_t k = 1; k <= nzo && (k == 1 || rows * k <= 32 * (int64_t)cus); ++k) {
+    const double exact = (double)(rows * k) / (4.0 * cus);
+    const double per_simd = exact < 8.0 ? ceil(exact) : exact;
+    const double planes = (double)((nzo + k - 1) / k + 2);
+    const double cost = planes * (0.4 * per_simd > 1.0 ? 0.4 * per_simd : 1.0);
+    if (cost < best) {
+      best = cost;
+      nzb = k;
+    }
+  }
+  return (int)nzb;
+}
+
+hipError_t launch_step_rows(const Layout& L, const void* src, void* dst, const StepParams& p, int nzb,
                             hipStream_t s) {
   RowsParams rp;
   rp.nx = (int)L.nx;
@@ -271,26 +299,10 @@ hipError_t launch_step_rows(const Layout& L, const void* src, void* dst, const S
   rp.zlo = p.fixed[2] ? 1 : 0;
   rp.nyo = rp.ny - 2 * rp.ylo;
   rp.nzo = rp.nz - 2 * rp.zlo;
-  rp.nseg = rp.xper ? (rp.nx + 61) / 62 : (rp.nx - 2 + 61) / 62;
-  const int64_t rows = (int64_t)rp.nseg * rp.nyo;
-  // Chunks of planes, by a model of the time: a plane step takes a wavefront about
-  // 1 us (its loads and chain) and a SIMD 0.4 us for each of its wavefronts, and
-  // a chunk also runs the two planes beside it. Up to eight wavefronts a SIMD
-  // the last, nearly empty round counts in full.
-  int64_t nzb = 1;
-  double best = 1e300;
-  for (int64_t k = 1; k <= rp.nzo && (k == 1 || rows * k <= 32 * (int64_t)cus); ++k) {
-    const double exact = (double)(rows * k) / (4.0 * cus);
-    const double per_simd = exact < 8.0 ? ceil(exact) : exact;
-    const double planes = (double)((rp.nzo + k - 1) / k + 2);
-    const double cost = planes * (0.4 * per_simd > 1.0 ? 0.4 * per_simd : 1.0);
-    if (cost < best) {
-      best = cost;
-      nzb = k;
-    }
-  }
-  rp.nzb = (int)nzb;
-  rp.nwaves = rows * nzb;
+  if (nzb < 1 || nzb > rp.nzo) return hipErrorInvalidValue;
+  rp.nseg = (int)row_segments(L, p);
+  rp.nzb = nzb;
+  rp.nwaves = (int64_t)rp.nseg * rp.nyo * nzb;
   rp.rho_ref = p.rho_ref;
   for (int i = 0; i < 3; ++i) rp.g[i] = p.g[i];
   rp.sr_key = p.sr_key;

@@ -24,8 +24,9 @@ struct Plan {
   FastShape s3;
   Fast2DShape s2;
   Multi2DShape multi;  // kernel 3: several steps per launch (steps 0: one)
-  Seg3DShape seg;      // kernel 0, FP64 D3Q19: its tiling, by the rule of seg3d_shape ...
-  int seg_fixed = -1;  // ... for these face kinds (bit k: axis k is bounded)
+  Seg3DShape seg;        // kernel 0, D3Q19: the tiling of the FP64 kernel ...
+  int rows_nzb = 1;      // ... or the chunks of planes of the row kernel, by their rules ...
+  int march_faces = -1;  // ... for these faces (bit k: axis k is bounded)
 };
 }  // namespace
 
@@ -45,7 +46,8 @@ struct maclab_s {
   int cus = 256;               // compute units of the device
   int device = 0;              // HIP device the handle was created on
   Plan plan;                   // kernel and tiling of the step
-  bool plan_set = false;       // chosen by maclab_set_tiling / maclab_autotune
+  bool plan_set = false;       // chosen by maclab_set_tiling / maclab_autotune, else the default ...
+  int plan_faces = -1;         // ... for these faces (bit k: axis k is bounded)
   int adj_kernel = -1;         // reverse step: -1 automatic, 0 general, 3 fast D2Q9
   Fast2DShape adj2;            // its tiling when set explicitly
   bool view = false;           // one lattice of a batch: memory owned by the batch
@@ -294,25 +296,31 @@ int plan_candidates(const Layout& L, const StepParams& p, int cus, Plan* out, in
   return n;
 }
 
-hipError_t launch_plan(const Layout& L, const StepParams& p, const Plan& pl, int cus, const void* src, void* dst,
+hipError_t launch_plan(const Layout& L, const StepParams& p, const Plan& pl, const void* src, void* dst,
                        hipStream_t s) {
   switch (pl.kernel) {
     case 1:
     case 2: return launch_step_fast(L, src, dst, p, pl.s3, s);
     case 3: return launch_step_fast2d(L, src, dst, p, pl.s2, s);
   }
-  if (pl.seg_fixed >= 0) return launch_step_seg(L, src, dst, p, pl.seg, s);
-  if (L.q == 19 && (L.precision != MACLAB_FP64 || L.N >= kMarchNodes64))
-    return launch_step_rows(L, src, dst, p, cus, s);
+  if (seg3d_supported(L)) return launch_step_seg(L, src, dst, p, pl.seg, s);
+  if (rows_march(L)) return launch_step_rows(L, src, dst, p, pl.rows_nzb, s);
   return launch_step_generic(L, src, dst, p, s);
 }
 
-// The tiling of the FP64 D3Q19 kernel for the lattice's current faces.
-void set_seg(const Layout& L, const StepParams& p, int cus, Plan* pl) {
-  const int fixed = (p.fixed[0] != 0) | (p.fixed[1] != 0) << 1 | (p.fixed[2] != 0) << 2;
-  if (pl->kernel != 0 || !seg3d_supported(L) || pl->seg_fixed == fixed) return;
-  pl->seg = seg3d_shape(L, p, cus);
-  pl->seg_fixed = fixed;
+int bounded_axes(const StepParams& p) {
+  return (p.fixed[0] != 0) | (p.fixed[1] != 0) << 1 | (p.fixed[2] != 0) << 2;
+}
+
+// The general kernel's march in z for the lattice's current faces.
+void set_march(const Layout& L, const StepParams& p, int cus, Plan* pl) {
+  const int faces = bounded_axes(p);
+  if (pl->kernel != 0 || pl->march_faces == faces) return;
+  if (seg3d_supported(L))
+    pl->seg = seg3d_shape(L, p, cus);
+  else if (rows_march(L))
+    pl->rows_nzb = rows_chunks(L, p, cus);
+  pl->march_faces = faces;
 }
 
 // Steps of the next launch when `left` are to do, at most `most` a launch: as
@@ -335,13 +343,15 @@ int64_t multi_launches(int64_t n, int most) {
 // step by step, derived faces change after every step.
 bool takes_several(maclab_t h) { return !h->view && !has_derived_faces(h->fv); }
 
+// The plan for the current faces. The default one is kept for them: ranking the shapes
+// of several steps takes a microsecond, the chunks of a long thin lattice twenty.
 const Plan& current_plan(maclab_t h, const StepParams& p) {
-  if (!(h->plan_set && plan_valid(h->L, p, h->plan))) {
-    const Plan pl = plan_default(h->L, p, h->cus);
-    if (pl.kernel != 0 || h->plan.kernel != 0) h->plan = pl;  // (the general kernel's tiling is kept while it runs)
+  if (h->plan_set ? !plan_valid(h->L, p, h->plan) : h->plan_faces != bounded_axes(p)) {
+    h->plan = plan_default(h->L, p, h->cus);
     h->plan_set = false;
+    h->plan_faces = bounded_axes(p);
   }
-  set_seg(h->L, p, h->cus, &h->plan);
+  set_march(h->L, p, h->cus, &h->plan);
   return h->plan;
 }
 
@@ -480,7 +490,7 @@ int maclab_step(maclab_t h, int64_t n) {
     if (m > 1) {
       HIP_TRY(h, launch_multi2d(h->L, src, dst, p, pl.multi, m, h->stream));
     } else {
-      HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, src, dst, h->stream));
+      HIP_TRY(h, launch_plan(h->L, p, pl, src, dst, h->stream));
       HIP_TRY(h, launch_derive_faces(h->L, dst, h->fv, h->stream));
     }
     h->cur ^= 1;
@@ -694,7 +704,7 @@ int maclab_autotune(maclab_t h, int reps, double* best_ms) {
   void* dst = h->state[h->cur ^ 1];  // scratch output: the state is not advanced
   Plan cand[96];
   const int nc = plan_candidates(h->L, p, h->cus, cand, 96);
-  for (int i = 0; i < nc; ++i) set_seg(h->L, p, h->cus, &cand[i]);
+  for (int i = 0; i < nc; ++i) set_march(h->L, p, h->cus, &cand[i]);
   hipEvent_t e0, e1;
   HIP_TRY(h, hipEventCreate(&e0));
   hipError_t ee = hipEventCreate(&e1);
@@ -749,7 +759,7 @@ int maclab_autotune(maclab_t h, int reps, double* best_ms) {
   double best = 1e300;
   int best_i = 0;
   for (int i = 0; i < nc && err == hipSuccess; ++i) {
-    const double per = timed(reps, [&] { return launch_plan(h->L, p, cand[i], h->cus, src, dst, h->stream); });
+    const double per = timed(reps, [&] { return launch_plan(h->L, p, cand[i], src, dst, h->stream); });
     if (err != hipSuccess) break;
     if (per < best) {
       best = per;
@@ -784,7 +794,7 @@ int maclab_step_external(maclab_t h, const void* src, void* dst, int64_t step_in
   p.step = (uint64_t)step_index;
   p.sr_key = sr_key(p.seed, p.step);
   const Plan pl = current_plan(h, p);
-  HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, src, dst, h->stream));
+  HIP_TRY(h, launch_plan(h->L, p, pl, src, dst, h->stream));
   bool any_bounded = false;
   for (int f = 0; f < 6; ++f) any_bounded |= h->fv.kind[f] != MACLAB_BC_PERIODIC;
   if (any_bounded) HIP_TRY(h, launch_impose_bc(h->L, dst, 0, 1, h->fv, h->cfg.rho_ref, h->e, h->stream));
@@ -932,7 +942,7 @@ int maclab_adjoint_segment(maclab_t h, const void* ckpt, void* states, int64_t n
       HIP_TRY(h, launch_multi2d_trace(h->L, slot(n - 1), (void*)slot(n), p, pl.multi, m, h->stream));
       n += m;
     } else {
-      HIP_TRY(h, launch_plan(h->L, p, pl, h->cus, slot(n - 1), (void*)slot(n), h->stream));
+      HIP_TRY(h, launch_plan(h->L, p, pl, slot(n - 1), (void*)slot(n), h->stream));
       ++n;
     }
   }
