@@ -44,10 +44,10 @@ struct Vec<T, 1> {
 // this 38); 251^3, whose rows end in part of a vector, 870 and 513; D2Q9 1024^2
 // 32 and 15. Fewer workgroups on a CU change the time by under 3%.
 //
-// Stores: past the caches for a state larger than the memory-side cache (256^3
-// 485 us, 500 device-scope, 504 cached), else device-scope, which leaves the state
-// there for the next step (D2Q9 1024^2 14.9 us, 19.3 non-temporal; D3Q19 64^3
-// 8.3, 11.1). The end of a row is stored as the rest of it is: non-temporal among
+// Stores: past the caches for a state that does not stay in the memory-side cache
+// between steps (256^3 485 us, 500 device-scope, 504 cached), else device-scope, which
+// leaves it there for the next step (D2Q9 1024^2 13.5 us, 19.3 non-temporal; D3Q19
+// 64^3 7.0, 9.0). The end of a row is stored as the rest of it is: non-temporal among
 // device-scope stores it cost 164 us a step against 94 (D3Q19 FP32 131^3).
 //
 // What a shifted vector takes from outside the row is replaced: on a periodic
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src
         o[e] = (T)Lt::wnum[a] * (r[e] + rho[e] * phim1) * (T)(1.0 / 36.0);
         if (KX > 1 && ((wall_lo && e == 0) || (wall_hi && i + e == nx - 1))) o[e] = edge[a];
       }
-      // device-scope: a state of under 256 MB, so a plane is within a buffer resource's range
+      // device-scope: a state of under kBgkStreamBytes, so a plane is within a buffer resource's range
       const buf_t to = make_buf(dst + (int64_t)a * p.plane, p.plane * (int)sizeof(T));
       const int off = (int)((own + i) * (int)sizeof(T));
       if (!TAIL || i + KX <= nx) {
@@ -243,9 +243,17 @@ __global__ void bgk_impose_kernel(T* b0, T* b1, BgkParams p, FaceValues fv, doub
   }
 }
 
+// Populations from here on stream. With the other buffer they take more than the 256 MB
+// cache, and by now it holds little of what the next step reads: us a step
+// device-scope and non-temporal, 139 MB 300x80x80 FP32 68.1, 69.5; 144 MB D2Q9 2048^2
+// FP32 49.2, 57.8; 152 MB 128^3 FP32 63.0, 61.8 (but 256x128x64 55.3, 59.4); 154 MB
+// D2Q9 1500^2 FP64 75.9, 75.3; 163 MB 104^3 FP64 71.5, 67.4; 182 MB 136^3 FP32 93.0, 80.5;
+// 254 MB 152^3 FP32 124.7, 109.9.
+constexpr size_t kBgkStreamBytes = size_t(150) << 20;
+
 template <int Q, class T, int KX, bool TAIL>
 hipError_t step_nt(const BgkParams& p, int groups, const void* src, void* dst, hipStream_t s) {
-  if ((size_t)Q * (size_t)p.plane * sizeof(T) >= kStreamStoreBytes)
+  if ((size_t)Q * (size_t)p.plane * sizeof(T) >= kBgkStreamBytes)
     hipLaunchKernelGGL((bgk_step_kernel<Q, T, KX, TAIL, true>), dim3((unsigned)groups), dim3(64, 4), 0, s,
                        (const T*)src, (T*)dst, p);
   else

@@ -140,3 +140,20 @@ for q, n, p, walls in ((19, (300, 67, 93), r.m.FP32, "yz"), (19, (130, 129, 131)
     la, lb = r.launches(r.lib.maclab_step, a, 9), r.launches(r.lib.maclab_step, b, 9)
     assert [e[:3] for e in la[1]] == [e[:3] for e in lb[1]], (n, walls)
 """)
+
+
+def test_populations_stream_from_the_size_where_that_was_faster(tmp_path):
+    standin.run(tmp_path, """
+import ctypes
+r = standin.load()
+lib, m = r.lib, r.m
+for q, n, p, streams in ((19, (300, 80, 80), m.FP32, 0), (19, (90, 90, 90), m.FP64, 0), (9, (2048, 2048), m.FP32, 0),
+                         (19, (104, 104, 104), m.FP64, 1), (19, (136, 136, 136), m.FP32, 1), (9, (2500, 2500), m.FP32, 1)):
+    c = r.config(q, n, p)
+    c.workspace, c.workspace_bytes = standin.WORKSPACE, lib.maclab_bgk_workspace_bytes(ctypes.byref(c))
+    h = ctypes.c_void_p()
+    assert lib.maclab_bgk_init(ctypes.byref(c), ctypes.byref(h)) == 0
+    rc, log = r.launches(lib.maclab_bgk_step, h, 1)
+    assert rc == 0 and len(log) == 1 and "bgk_step_kernel" in log[0][0]
+    assert f"Lb{streams}EEEv" in log[0][0], (n, log[0][0])  # the kernel's last template argument
+""")
