@@ -63,9 +63,13 @@ __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src
   const int64_t nb = gridDim.x, bid = blockIdx.x;
   const int64_t per = nb >> 3, rem = nb & 7, xcd = bid & 7;
   const int64_t grp = xcd * per + (xcd < rem ? xcd : rem) + (bid >> 3);
-  const int64_t row = grp * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  // One node per lane: a row is short, and its addresses are formed faster per lane than
+  // in the scalar unit (twice the instructions: 4x60x60 FP32 7.4 us a step against 6.6).
+  const int64_t row = grp * 4 + (KX == 1 ? (int)threadIdx.y : __builtin_amdgcn_readfirstlane((int)threadIdx.y));
   if (row >= rows) return;
-  const int64_t j = row % p.ny, k = row / p.ny;
+  // (a 64-bit division is a long chain, and few lattices have so many rows)
+  const int64_t k = rows <= 0x7fffffff ? (int64_t)((uint32_t)row / (uint32_t)p.ny) : row / p.ny;
+  const int64_t j = row - k * p.ny;
   if ((p.fixed[1] && (j == 0 || j == p.ny - 1)) || (p.fixed[2] && (k == 0 || k == p.nz - 1))) return;
   // upstream rows (an interior node of a fixed axis never wraps)
   const int64_t jr[3] = {j + 1 < p.ny ? j + 1 : 0, j, j > 0 ? j - 1 : p.ny - 1};  // index 1 - c_y
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src
         o[e] = (T)Lt::wnum[a] * (r[e] + rho[e] * phim1) * (T)(1.0 / 36.0);
         if (KX > 1 && ((wall_lo && e == 0) || (wall_hi && i + e == nx - 1))) o[e] = edge[a];
       }
-      // device-scope: a state of under kBgkStreamBytes, so a plane is within a buffer resource's range
+      // device-scope: a state of under 148 MB, so a plane is within a buffer resource's range
       const buf_t to = make_buf(dst + (int64_t)a * p.plane, p.plane * (int)sizeof(T));
       const int off = (int)((own + i) * (int)sizeof(T));
       if (!TAIL || i + KX <= nx) {
@@ -243,17 +247,26 @@ __global__ void bgk_impose_kernel(T* b0, T* b1, BgkParams p, FaceValues fv, doub
   }
 }
 
-// Populations from here on stream. With the other buffer they take more than the 256 MB
-// cache, and by now it holds little of what the next step reads: us a step
-// device-scope and non-temporal, 139 MB 300x80x80 FP32 68.1, 69.5; 144 MB D2Q9 2048^2
-// FP32 49.2, 57.8; 152 MB 128^3 FP32 63.0, 61.8 (but 256x128x64 55.3, 59.4); 154 MB
-// D2Q9 1500^2 FP64 75.9, 75.3; 163 MB 104^3 FP64 71.5, 67.4; 182 MB 136^3 FP32 93.0, 80.5;
-// 254 MB 152^3 FP32 124.7, 109.9.
-constexpr size_t kBgkStreamBytes = size_t(150) << 20;
+template <int Q, class T>
+size_t state_bytes(const BgkParams& p) {
+  return (size_t)Q * (size_t)p.plane * sizeof(T);
+}
+
+// Whether the stores stream past the caches: where the two buffers no longer fit the
+// 256 MB cache together and it holds little of what the next step reads. Time against one
+// node per lane and streaming stores, widths of 32 to 1000 nodes: 120 MB device-scope
+// 0.51..0.90, streaming 0.70..1.15; 140 MB 0.63..1.10 and 0.65..1.07; 160 MB device-scope
+// about 1.03 (104^3 FP64 71.5 us a step, 67.4 streaming), 200 MB and more slower.
+// Rows of 20 nodes lose from the sum of 256 MB on (140 MB 1.17). Fewer than
+// eight rows are over before a device-scope store is (D2Q9 140x4 FP64 4.2, 3.7).
+template <int Q, class T>
+bool streams(const BgkParams& p) {
+  return state_bytes<Q, T>(p) >= size_t(p.nx < 32 ? 128 : 148) << 20 || p.ny * p.nz < 8;
+}
 
 template <int Q, class T, int KX, bool TAIL>
 hipError_t step_nt(const BgkParams& p, int groups, const void* src, void* dst, hipStream_t s) {
-  if ((size_t)Q * (size_t)p.plane * sizeof(T) >= kBgkStreamBytes)
+  if (streams<Q, T>(p))
     hipLaunchKernelGGL((bgk_step_kernel<Q, T, KX, TAIL, true>), dim3((unsigned)groups), dim3(64, 4), 0, s,
                        (const T*)src, (T*)dst, p);
   else
@@ -270,12 +283,35 @@ hipError_t step_kx(const BgkParams& p, const void* src, void* dst, hipStream_t s
   return step_nt<Q, T, KX, false>(p, (int)groups, src, dst, s);
 }
 
-// Nodes per lane: a 16-byte access, as long as half of the lanes of a row have
-// one (160^3 FP32: 122 us a step against 153 with one node per lane).
+// Nodes per lane. A 16-byte access pays for what memory bounds; a smaller lattice is
+// bound by the chain of a row (loads, edge values, stores), which is longer with more
+// nodes per lane: D3Q19 FP32 129x16x16 7.9 us a step against 4.8, FP64 129x59x3 13.4
+// against 5.5.
+template <int Q, class T>
+bool wide(const BgkParams& p) {
+  constexpr int most = 16 / (int)sizeof(T);
+  const size_t bytes = state_bytes<Q, T>(p);
+  if (p.nx < 32 * most || p.ny * p.nz < 16) return false;
+  if (bytes >= kStreamStoreBytes) return true;
+  // Two nodes have to save more than a third of a row's passes (140 MB, against one node
+  // per lane: 100 and 193 nodes 0.87, 0.92; 64, 129 and 160 nodes 1.03, 1.09, 1.07).
+  const int64_t one = (p.nx + 63) / 64, vec = (p.nx + 64 * most - 1) / (64 * most);
+  if (most == 2 && (2 * one <= 3 * vec || p.nx < 80)) return false;
+  if (streams<Q, T>(p)) return true;
+  // Within the cache, time wide and with one node per lane, against one node and streaming
+  // stores: D2Q9 FP32 0.43..0.96 and 0.62..0.84 from 1 MB, FP64 0.57..0.78 and 0.57..0.68
+  // at 40 MB; D3Q19 FP32 0.55..0.88 and 0.62..0.76 at 40 MB (0.71..1.08 and 0.72..0.88 at
+  // 20), FP64 0.58..0.94 and 0.59..0.75 at 60 MB. Rows of eight passes and more gain at any
+  // size in FP64 (D2Q9 600x60 9.1 and 10.8 us a step, 1000x291 13.2 and 16.1); FP32
+  // rows of 128 nodes, half a vector row, do not (D3Q19 20..120 MB 0.69..1.18 and 0.60..0.78).
+  if (most == 4 && p.nx == 128) return false;
+  if (most == 2 && p.nx >= 512) return true;
+  return bytes >= size_t(Q == 9 ? (most == 4 ? 0 : 40) : (most == 4 ? 40 : 60)) << 20;
+}
+
 template <int Q, class T>
 hipError_t step_qt(const BgkParams& p, const void* src, void* dst, hipStream_t s) {
-  constexpr int most = 16 / (int)sizeof(T);
-  if (p.nx >= 32 * most) return step_kx<Q, T, most>(p, src, dst, s);
+  if (wide<Q, T>(p)) return step_kx<Q, T, 16 / (int)sizeof(T)>(p, src, dst, s);
   return step_kx<Q, T, 1>(p, src, dst, s);
 }
 

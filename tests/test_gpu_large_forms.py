@@ -1,6 +1,5 @@
 """Forms of the step kernels that only larger lattices reach, against the FP64
 oracle or against a form that is itself checked against it."""
-import numpy as np
 import pytest
 
 import oracle
@@ -19,20 +18,32 @@ def _boxed(q, n, walls, seed=3):
     return case
 
 
-# Populations past 256 MB, whose stores stream, in rows that end in part of a vector
-# (four nodes FP32, two FP64). Tolerances as for the other population tests.
-@pytest.mark.parametrize("precision,n,tol", [("fp32", (157, 155, 150), 1e-5), ("fp32", (1030, 60, 60), 1e-5),
-                                             ("fp64", (125, 130, 110), 1e-12)])
-@pytest.mark.parametrize("walls", ["", "xyz"])
-def test_population_rows_past_the_memory_side_cache(precision, n, tol, walls):
+# The population step's forms: (lattice, nodes, storage, nodes per lane, streaming stores).
+# Rows that end in part of a vector and rows that do not, a wavefront's pass and more;
+# test_host_sequence.py checks that these lattices take these forms.
+POPULATIONS = [
+    (9, (129, 17, 1), "fp32", 4, False), (9, (130, 17, 1), "fp32", 4, False), (9, (131, 33, 1), "fp32", 4, False),
+    (9, (256, 16, 1), "fp32", 4, False), (9, (257, 18, 1), "fp32", 4, False), (9, (515, 20, 1), "fp32", 4, False),
+    (9, (512, 17, 1), "fp64", 2, False), (9, (641, 16, 1), "fp64", 2, False), (9, (513, 7, 1), "fp64", 1, True),
+    (9, (400, 16, 1), "fp64", 1, False), (19, (129, 66, 67), "fp32", 4, False), (19, (130, 66, 67), "fp32", 4, False),
+    (19, (260, 50, 45), "fp32", 4, False), (19, (193, 48, 48), "fp64", 2, False), (19, (254, 42, 42), "fp64", 2, False),
+    (19, (20, 260, 380), "fp32", 1, True), (19, (157, 155, 150), "fp32", 4, True), (19, (1030, 60, 60), "fp32", 4, True),
+    (19, (125, 130, 110), "fp64", 2, True), (19, (128, 110, 80), "fp64", 2, True),
+]
+
+
+# Tolerances as for the other population tests.
+@pytest.mark.parametrize("q,n,precision,lanes,streams", POPULATIONS)
+@pytest.mark.parametrize("walls", ["", "xyz", "x"])
+def test_population_forms(q, n, precision, lanes, streams, walls):
     print(f"[bgk] {n} {walls} {precision}", flush=True)
-    case = _boxed(19, n, walls)
-    sim = BGK(19, n, case.dx, case.nu, precision=precision, body_force=case.G)
-    assert 19 * np.prod(n) * (4 if precision == "fp32" else 8) > 256 << 20
+    case = _boxed(q, n, walls[: 2 if q == 9 else 3])
+    sim = BGK(q, n, case.dx, case.nu, precision=precision, body_force=case.G)
     for f, (rb, ub) in case.fixed.items():
         sim.set_bc(f, rb, ub)
     sim.set_fields(case.rho, case.u)
     sim.step(2)
     rho, u = sim.fields()
     orho, ou = oracle.run(to_problem(case), case.rho, case.u, 2)
+    tol = 1e-5 if precision == "fp32" else 1e-12
     assert rel_l2(u, ou) < tol and rel_l2(rho, orho) < tol

@@ -142,18 +142,27 @@ for q, n, p, walls in ((19, (300, 67, 93), r.m.FP32, "yz"), (19, (130, 129, 131)
 """)
 
 
-def test_populations_stream_from_the_size_where_that_was_faster(tmp_path):
-    standin.run(tmp_path, """
+def test_population_forms(tmp_path):
+    """Nodes per lane and store policy: the lattices of the GPU test of these forms, and
+    the sizes where the policy was measured to change sides."""
+    from test_gpu_large_forms import POPULATIONS
+
+    more = [(19, (128, 128, 128), "fp32", 4, True), (19, (104, 104, 104), "fp64", 2, True), (19, (64, 64, 64), "fp32", 1, False),
+            (19, (129, 16, 16), "fp32", 1, False), (19, (129, 59, 3), "fp64", 1, False), (19, (300, 80, 80), "fp32", 4, False),
+            (19, (160, 90, 90), "fp64", 1, True), (19, (256, 256, 256), "fp32", 4, True), (9, (2048, 2048, 1), "fp32", 4, False),
+            (9, (1024, 1024, 1), "fp64", 2, False), (9, (140, 4, 1), "fp64", 1, True)]
+    standin.run(tmp_path, f"""
 import ctypes
 r = standin.load()
 lib, m = r.lib, r.m
-for q, n, p, streams in ((19, (300, 80, 80), m.FP32, 0), (19, (90, 90, 90), m.FP64, 0), (9, (2048, 2048), m.FP32, 0),
-                         (19, (104, 104, 104), m.FP64, 1), (19, (136, 136, 136), m.FP32, 1), (9, (2500, 2500), m.FP32, 1)):
-    c = r.config(q, n, p)
+for q, n, p, lanes, streams in {POPULATIONS + more}:
+    c = r.config(q, n, m.FP64 if p == "fp64" else m.FP32)
     c.workspace, c.workspace_bytes = standin.WORKSPACE, lib.maclab_bgk_workspace_bytes(ctypes.byref(c))
     h = ctypes.c_void_p()
     assert lib.maclab_bgk_init(ctypes.byref(c), ctypes.byref(h)) == 0
     rc, log = r.launches(lib.maclab_bgk_step, h, 1)
-    assert rc == 0 and len(log) == 1 and "bgk_step_kernel" in log[0][0]
-    assert f"Lb{streams}EEEv" in log[0][0], (n, log[0][0])  # the kernel's last template argument
+    assert rc == 0 and len(log) == 1
+    tail = lanes > 1 and n[0] % lanes != 0
+    want = f"bgk_step_kernelILi{{q}}E{{'d' if p == 'fp64' else 'f'}}Li{{lanes}}ELb{{int(tail)}}ELb{{int(streams)}}E"
+    assert want in log[0][0], (q, n, p, want, log[0][0])
 """)
