@@ -88,8 +88,11 @@ __global__ __launch_bounds__(64 * kRowsWaves) void step_d3q19_rows(const typenam
   const int yb = p.yper && y == 0 ? p.ny - 1 : y - 1, ya = p.yper && y == p.ny - 1 ? 0 : y + 1;
   // periodic: the segment's first node is in lane 1; walls: node 0 is in lane 0
   const int x = seg * 62 + lane - (p.xper ? 1 : 0);
-  // the position this lane loads: wrapped, or the wall for lanes past it
-  const int xl = p.xper ? (x < 0 ? x + p.nx : (x < p.nx ? x : x % p.nx)) : (x < p.nx ? x : p.nx - 1);
+  // The position this lane loads: the first node for the lane past the last one on a
+  // periodic axis, or the wall; no stored node depends on the lanes beyond, which load the
+  // same. (A remainder for them cost 0.5 us a step, 16x40x40 FP32 5.7 against 4.7 with
+  // one thread per node.)
+  const int xl = p.xper ? (x < 0 ? p.nx - 1 : (x < p.nx ? x : 0)) : (x < p.nx ? x : p.nx - 1);
   const bool stores = lane > 0 && lane < 63 && x < p.nx - (p.xper ? 0 : 1);
   // (a remainder would be some thirty instructions)
   auto zwrap = [&](int z) { return z < 0 ? z + p.nz : (z >= p.nz ? z - p.nz : z); };
