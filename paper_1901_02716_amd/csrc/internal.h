@@ -105,14 +105,10 @@ hipError_t launch_step_fast(const Layout& L, const void* src, void* dst, const S
                             hipStream_t s);
 
 // D3Q19, any lattice (kernels_rows.hip), in nzb chunks of planes; rows_chunks: the
-// chunks for a lattice and its faces. rows_march: whether the general kernel takes this
-// form (where the FP64 path below does not apply).
+// chunks for a lattice and its faces.
 hipError_t launch_step_rows(const Layout& L, const void* src, void* dst, const StepParams& p, int nzb, hipStream_t s);
 int rows_chunks(const Layout& L, const StepParams& p, int cus);
-bool rows_march(const Layout& L);
-// Nodes from which the FP64 D3Q19 step is worth a march in z: below, the chain
-// of plane steps (6.5 us at 20k nodes, against 4.8) takes longer than one thread
-// per node with all its loads at once.
+// Nodes from which the FP64 D3Q19 step may be worth a march in z (by rows, or as below).
 constexpr int64_t kMarchNodes64 = 40960;
 
 // FP64 D3Q19 path (kernels_seg.hip), the general kernel's form for FP64: rows
@@ -122,6 +118,7 @@ struct Seg3DShape {
   int kx = 1, w = 6, nyb = 1, nzb = 1;
 };
 bool seg3d_supported(const Layout& L);
+bool seg3d_pays(const Layout& L, const StepParams& p, int cus);
 Seg3DShape seg3d_shape(const Layout& L, const StepParams& p, int cus);
 hipError_t launch_step_seg(const Layout& L, const void* src, void* dst, const StepParams& p, const Seg3DShape& sh,
                            hipStream_t s);

@@ -259,8 +259,6 @@ static hipError_t launch_rows(const Layout& L, const void* src, void* dst, const
   return hipGetLastError();
 }
 
-bool rows_march(const Layout& L) { return L.q == 19 && (L.precision != MACLAB_FP64 || L.N >= kMarchNodes64); }
-
 static int64_t row_segments(const Layout& L, const StepParams& p) {
   return p.fixed[0] ? (L.nx - 2 + 61) / 62 : (L.nx + 61) / 62;
 }

@@ -276,6 +276,17 @@ bool seg3d_supported(const Layout& L) {
          L.plane * L.bytes < (int64_t(1) << 31);
 }
 
+// One thread per node, with all its loads at once, takes 4.8 us a step as long as every
+// SIMD has one wavefront (64 nodes of a row) at most; the chain of plane steps takes 5.2 to
+// 6.5 (40x32x32 4.8 and 5.2 between walls, 4.8 and 6.4 periodic; 63x32x32 4.9, 6.5).
+// With more wavefronts it is 7 and up (46x32 rows 7.6 and 6.5, 12x100x30 9.7 and 7.5), but
+// not with one output row, where six of a workgroup's eight rows are idle (80x3x800
+// 7.4 and 9.8, 300x3x800 even).
+bool seg3d_pays(const Layout& L, const StepParams& p, int cus) {
+  const int64_t nyo = p.fixed[1] ? L.ny - 2 : L.ny, nzo = p.fixed[2] ? L.nz - 2 : L.nz;
+  return (L.nx + 63) / 64 * nyo * nzo > 4 * (int64_t)cus && nyo > 1;
+}
+
 // The tiling, from a model of the time: a workgroup's plane step costs each of
 // its wavefronts a share of its CU for every node a lane holds (0.11 us per
 // wavefront and node; a fifth more with one node per lane, half as much again

@@ -24,8 +24,10 @@ struct Plan {
   FastShape s3;
   Fast2DShape s2;
   Multi2DShape multi;  // kernel 3: several steps per launch (steps 0: one)
-  Seg3DShape seg;        // kernel 0, D3Q19: the tiling of the FP64 kernel ...
-  int rows_nzb = 1;      // ... or the chunks of planes of the row kernel, by their rules ...
+  // kernel 0: one thread per node, or for D3Q19 a march in z ...
+  enum March { kNodes, kSegments, kRows } march = kNodes;
+  Seg3DShape seg;        // ... with this tiling (kSegments) ...
+  int rows_nzb = 1;      // ... or these chunks of planes (kRows), by their rules ...
   int march_faces = -1;  // ... for these faces (bit k: axis k is bounded)
 };
 }  // namespace
@@ -303,8 +305,8 @@ hipError_t launch_plan(const Layout& L, const StepParams& p, const Plan& pl, con
     case 2: return launch_step_fast(L, src, dst, p, pl.s3, s);
     case 3: return launch_step_fast2d(L, src, dst, p, pl.s2, s);
   }
-  if (seg3d_supported(L)) return launch_step_seg(L, src, dst, p, pl.seg, s);
-  if (rows_march(L)) return launch_step_rows(L, src, dst, p, pl.rows_nzb, s);
+  if (pl.march == Plan::kSegments) return launch_step_seg(L, src, dst, p, pl.seg, s);
+  if (pl.march == Plan::kRows) return launch_step_rows(L, src, dst, p, pl.rows_nzb, s);
   return launch_step_generic(L, src, dst, p, s);
 }
 
@@ -312,14 +314,20 @@ int bounded_axes(const StepParams& p) {
   return (p.fixed[0] != 0) | (p.fixed[1] != 0) << 1 | (p.fixed[2] != 0) << 2;
 }
 
-// The general kernel's march in z for the lattice's current faces.
+// The general kernel's form for the lattice's current faces.
 void set_march(const Layout& L, const StepParams& p, int cus, Plan* pl) {
   const int faces = bounded_axes(p);
   if (pl->kernel != 0 || pl->march_faces == faces) return;
-  if (seg3d_supported(L))
-    pl->seg = seg3d_shape(L, p, cus);
-  else if (rows_march(L))
+  pl->march = Plan::kNodes;
+  if (seg3d_supported(L)) {
+    if (seg3d_pays(L, p, cus)) {
+      pl->march = Plan::kSegments;
+      pl->seg = seg3d_shape(L, p, cus);
+    }
+  } else if (L.q == 19 && (L.precision != MACLAB_FP64 || L.N >= kMarchNodes64)) {
+    pl->march = Plan::kRows;
     pl->rows_nzb = rows_chunks(L, p, cus);
+  }
   pl->march_faces = faces;
 }
 

@@ -166,3 +166,17 @@ for q, n, p, lanes, streams in {POPULATIONS + more}:
     want = f"bgk_step_kernelILi{{q}}E{{'d' if p == 'fp64' else 'f'}}Li{{lanes}}ELb{{int(tail)}}ELb{{int(streams)}}E"
     assert want in log[0][0], (q, n, p, want, log[0][0])
 """)
+
+
+def test_fp64_d3q19_marches_where_that_was_faster(tmp_path):
+    standin.run(tmp_path, """
+r = standin.load()
+nodes, march = "step_generic_kernel", "step_d3q19_seg"
+for n, walls, want in (((40, 32, 32), "", nodes), ((63, 32, 32), "xyz", nodes), ((40, 33, 32), "", march), ((130, 8, 40), "xyz", nodes),
+                       ((130, 8, 50), "", march), ((80, 3, 800), "xyz", nodes), ((80, 3, 800), "", march), ((300, 3, 800), "xyz", nodes),
+                       ((48, 40, 36), "xyz", march), ((12, 100, 30), "", nodes), ((251, 251, 251), "xyz", march),
+                       ((200, 2, 130), "", "step_d3q19_rows"), ((100, 2, 130), "", nodes)):
+    h = r.handle(19, n, r.m.FP64, walls)
+    rc, log = r.launches(r.lib.maclab_step, h, 1)
+    assert rc == 0 and want in log[0][0], (n, walls, log)
+""")
