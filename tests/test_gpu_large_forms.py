@@ -1,10 +1,11 @@
 """Forms of the step kernels that only larger lattices reach, against the FP64
 oracle or against a form that is itself checked against it."""
+import numpy as np
 import pytest
 
 import oracle
 from conftest import rel_l2, to_problem
-from paper_1901_02716_amd import BGK, workloads
+from paper_1901_02716_amd import BGK, Simulation, workloads
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +48,36 @@ def test_population_forms(q, n, precision, lanes, streams, walls):
     orho, ou = oracle.run(to_problem(case), case.rho, case.u, 2)
     tol = 1e-5 if precision == "fp32" else 1e-12
     assert rel_l2(u, ou) < tol and rel_l2(rho, orho) < tol
+
+
+# The FP64 D3Q19 march: (nodes, walls, (nodes per lane, output rows of a workgroup, nodes
+# beside a segment evaluated, streaming stores)). Odd and even widths, with and without
+# padding of the row, a segment that the row ends in or fills; workgroups whose rows do
+# not divide the lattice's. test_host_sequence.py checks that they take these forms.
+SEGMENTS = [
+    ((64, 60, 50), "", (1, 6, 0, 0)), ((42, 40, 198), "xyz", (1, 6, 0, 0)), ((129, 40, 40), "", (1, 6, 1, 0)),
+    ((199, 155, 14), "xyz", (1, 6, 1, 0)), ((295, 104, 286), "xyz", (1, 6, 1, 1)), ((44, 195, 141), "xyz", (1, 14, 0, 0)),
+    ((28, 122, 220), "", (1, 14, 1, 0)), ((130, 129, 131), "xyz", (1, 14, 1, 0)), ((255, 169, 141), "", (1, 14, 1, 0)),
+    ((259, 185, 181), "yz", (1, 14, 1, 1)), ((60, 380, 375), "xyz", (1, 14, 0, 1)), ((98, 143, 60), "xy", (2, 6, 0, 0)),
+    ((119, 145, 50), "xy", (2, 6, 0, 0)), ((128, 128, 128), "xyz", (2, 6, 0, 0)), ((128, 128, 128), "", (2, 6, 0, 0)),
+    ((70, 297, 17), "", (2, 6, 1, 0)), ((96, 96, 96), "", (2, 6, 1, 0)), ((249, 130, 130), "xyz", (2, 6, 1, 0)),
+    ((250, 64, 64), "yz", (2, 6, 1, 0)), ((200, 60, 60), "xyz", (2, 6, 1, 0)), ((119, 239, 308), "x", (2, 6, 0, 1)),
+    ((106, 266, 315), "xyz", (2, 6, 0, 1)), ((251, 187, 183), "xyz", (2, 6, 1, 1)), ((150, 189, 303), "", (2, 6, 1, 1)),
+]
+
+
+# Tolerance of the other FP64 parity tests (a step rounds about 40 operations on values of
+# the size of u). Two steps: the second reads what the first stored, walls included.
+@pytest.mark.parametrize("n,walls,form", SEGMENTS)
+def test_fp64_march_forms(n, walls, form):
+    print(f"[march] {n} {walls} {form}", flush=True)
+    case = _boxed(19, n, walls)
+    sim = Simulation(19, n, case.dx, case.nu, precision="fp64", body_force=case.G)
+    sim.set_fields(case.rho, case.u)
+    for f, (rb, ub) in case.fixed.items():
+        sim.set_bc(f, rb, ub)
+    sim.step(2)
+    rho, u = sim.fields()
+    orho, ou = oracle.run(to_problem(case), case.rho, case.u, 2)
+    assert rel_l2(u, ou) < 1e-12 and rel_l2(rho, orho) < 1e-12
+    assert np.abs(u - ou).max() < 4e-12 * np.abs(ou).max()  # no single node stands out either

@@ -180,3 +180,18 @@ for n, walls, want in (((40, 32, 32), "", nodes), ((63, 32, 32), "xyz", nodes), 
     rc, log = r.launches(r.lib.maclab_step, h, 1)
     assert rc == 0 and want in log[0][0], (n, walls, log)
 """)
+
+
+def test_fp64_march_forms(tmp_path):
+    """The lattices of the GPU test of these forms."""
+    from test_gpu_large_forms import SEGMENTS
+
+    standin.run(tmp_path, f"""
+import re
+r = standin.load()
+for n, walls, (kx, w, halo, streams) in {SEGMENTS}:
+    rc, log = r.launches(r.lib.maclab_step, r.handle(19, n, r.m.FP64, walls), 1)
+    got = re.search("step_d3q19_segI.*?Li(\\d+)ELi(\\d+)ELb(\\d)ELi(\\d+)E", log[0][0])
+    policy = 2 if streams else 16
+    assert rc == 0 and got and tuple(map(int, got.groups())) == (kx, w, halo, policy), (n, walls, log[0][0])
+""")
