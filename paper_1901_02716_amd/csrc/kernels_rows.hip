@@ -11,12 +11,10 @@
 //    evaluates the 19 links of Eq. (2) that reach its row where they start, and
 //    moves them in x by DPP wave rotates. Links that move up a plane wait in
 //    registers.
-//  - The links of a node are then summed in the order of the lattice table, as a
-//    plain gather does: Eqs. (4)-(5) with the same bits as one thread per node
-//    that loads its 19 upstream nodes, whose 76 loads a node are what this form
-//    saves (300x67x93 FP32:
-//    34.3 us a step, 18.7 here; 200x200x120 FP32 99.7, 43.9, S16 104, 45.7). Bound by
-//    instructions: about 240 a wavefront and plane.
+//  - The links of a node are then summed in the order of the lattice table, as one
+//    thread per node does that loads its 19 upstream nodes; those 76 loads a node are
+//    what this form saves (300x67x93 FP32: 34.3 us a step, 18.7 here; 200x200x120 FP32
+//    99.7, 43.9, S16 104, 45.7). Bound by instructions: about 240 a wavefront and plane.
 #include "internal.h"
 
 #include <math.h>

@@ -2,6 +2,7 @@
 oracle or against a form that is itself checked against it."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from conftest import rel_l2, to_problem
@@ -81,3 +82,95 @@ def test_fp64_march_forms(n, walls, form):
     orho, ou = oracle.run(to_problem(case), case.rho, case.u, 2)
     assert rel_l2(u, ou) < 1e-12 and rel_l2(rho, orho) < 1e-12
     assert np.abs(u - ou).max() < 4e-12 * np.abs(ou).max()  # no single node stands out either
+
+
+def _random_state(sim, seed):
+    """Fields of the amplitudes of workloads.random_field, made on the device."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    shape = (sim.n[2], sim.n[1], sim.n[0])
+    e = sim.params()["e"]
+    rho = 1 + 0.01 * torch.randn(shape, generator=g, device="cuda", dtype=torch.float64)
+    u = 0.01 * e * torch.randn((sim.d,) + shape, generator=g, device="cuda", dtype=torch.float64)
+    sim.set_fields(rho, u)
+
+
+# Several D2Q9 steps per launch under the default and the tuned plan against one step per
+# launch, past 256 MB (streaming stores) and at the benchmark's sizes: the same bits.
+@pytest.mark.parametrize("n,walls,precision", [((4096, 4096), "xy", "fp64"), ((4700, 4901), "x", "fp32"),
+                                               ((4901, 4700), "", "hilo"), ((6700, 6901), "y", "s16"),
+                                               ((1024, 1024), "xy", "fp64"), ((1024, 1024), "xy", "fp32"),
+                                               ((512, 512), "", "fp32")])
+def test_several_steps_of_large_d2q9_lattices(n, walls, precision):
+    print(f"[multi] {n} {walls} {precision}", flush=True)
+    a, b = (Simulation(9, n, 1 / (n[1] - 1), 1e-4, precision=precision, seed=6) for _ in range(2))
+    _random_state(a, 9)
+    for ax in walls:
+        for side, v in (("lo", 0.0), ("hi", 0.05)):
+            a.set_bc(ax + side, 1.0, (v, 0.0, 0.0))
+            b.set_bc(ax + side, 1.0, (v, 0.0, 0.0))
+    b.load_state(a.save_state())
+    for tuned in (False, True):
+        if tuned:
+            a.autotune(reps=3)
+        a.step(18)
+        for _ in range(18):
+            b.step(1)
+        assert torch.equal(a.save_state(), b.save_state()), tuned
+        assert a.residual() == b.residual()
+
+
+def test_general_d3q19_lattice_whose_grid_needs_two_dimensions():
+    """A thin lattice with more workgroups than one grid dimension takes, periodic with a
+    period of seven rows: every period has the bits of the lattice of one."""
+    n, period = (65, 7 * 1198373, 1), (65, 7, 1)
+    small, big = (Simulation(19, m, 0.1, 0.05, precision="fp32", body_force=(0.1, 0.2, -0.1)) for m in (period, n))
+    assert 2 * n[1] > 4 << 22  # wavefronts: two segments a row, four to a workgroup, 2^22 workgroups
+    _random_state(small, 3)
+    cells = 65 * 7
+
+    def planes(sim, state):
+        return state.view(torch.float32).view(4, -1)[:, : sim.N]
+
+    s = planes(small, small.save_state())
+    start = torch.zeros(big.state_bytes(), dtype=torch.uint8, device="cuda")
+    planes(big, start).view(4, -1, cells).copy_(s.view(4, 1, cells).expand(4, n[1] // 7, cells))
+    big.load_state(start)
+    small.step(3)
+    big.step(3)
+    s = planes(small, small.save_state())
+    got = planes(big, big.save_state(out=start))
+    for f in range(4):
+        assert bool((got[f].view(-1, cells) == s[f]).all()), f
+
+
+@pytest.mark.parametrize("n", [(200, 2, 130), (61, 390, 2), (62, 1, 662), (63, 720, 1), (187, 3, 2), (330, 2, 131)])
+@pytest.mark.parametrize("walls", ["", "x"])
+def test_fp64_rows(n, walls):
+    """FP64 lattices with an axis too short for the march in segments: by rows from 40960
+    nodes, below with one thread per node. Tolerance as above."""
+    case = _boxed(19, n, walls)
+    sim = Simulation(19, n, case.dx, case.nu, precision="fp64", body_force=case.G)
+    sim.set_fields(case.rho, case.u)
+    for f, (rb, ub) in case.fixed.items():
+        sim.set_bc(f, rb, ub)
+    sim.step(4)
+    rho, u = sim.fields()
+    orho, ou = oracle.run(to_problem(case), case.rho, case.u, 4)
+    assert rel_l2(u, ou) < 1e-12 and rel_l2(rho, orho) < 1e-12
+
+
+# Split storage keeps a value to 2^-17 of it (7.6e-6); six roundings (the start and five
+# steps) and FP32 arithmetic stay under 1e-4.
+@pytest.mark.parametrize("n", [(3, 3, 3), (24, 11, 7), (61, 7, 4), (63, 9, 4), (125, 6, 4), (187, 60, 40)])
+@pytest.mark.parametrize("walls", ["", "xyz"])
+def test_split_storage_rows(n, walls):
+    case = _boxed(19, n, walls)
+    sim = Simulation(19, n, case.dx, case.nu, precision="hilo", body_force=case.G)
+    sim.set_fields(case.rho, case.u)
+    for f, (rb, ub) in case.fixed.items():
+        sim.set_bc(f, rb, ub)
+    sim.set_tiling(kernel="general")
+    sim.step(5)
+    rho, u = sim.fields()
+    orho, ou = oracle.run(to_problem(case), case.rho, case.u, 5)
+    assert rel_l2(u, ou) < 1e-4 and rel_l2(rho - 1, orho - 1) < 1e-4
