@@ -930,7 +930,7 @@ int maclab_adjoint_segment(maclab_t h, const void* ckpt, void* states, int64_t n
   // recomputed state holds the handle's face values, not the checkpoint's; the
   // others then take them from the state before (several steps), or find them
   // written into all states beforehand (a step leaves fixed nodes alone).
-  const Plan pl = current_plan(h, p);
+  const Plan pl = nsteps > 1 ? current_plan(h, p) : Plan{};
   const bool bounded = p.fixed[0] || p.fixed[1] || p.fixed[2];
   const bool several = pl.kernel == 3 && pl.multi.steps > 1;
   int64_t n = 1;
