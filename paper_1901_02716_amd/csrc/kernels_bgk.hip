@@ -302,9 +302,10 @@ bool wide(const BgkParams& p) {
   // stores: D2Q9 FP32 0.43..0.96 and 0.62..0.84 from 1 MB, FP64 0.57..0.78 and 0.57..0.68
   // at 40 MB; D3Q19 FP32 0.55..0.88 and 0.62..0.76 at 40 MB (0.71..1.08 and 0.72..0.88 at
   // 20), FP64 0.58..0.94 and 0.59..0.75 at 60 MB. Rows of eight passes and more gain at any
-  // size in FP64 (D2Q9 600x60 9.1 and 10.8 us a step, 1000x291 13.2 and 16.1); FP32
-  // rows of 128 nodes, half a vector row, do not (D3Q19 20..120 MB 0.69..1.18 and 0.60..0.78).
-  if (most == 4 && p.nx == 128) return false;
+  // size in FP64 (D2Q9 600x60 9.1 and 10.8 us a step, 1000x291 13.2 and 16.1). Four FP32
+  // nodes have to save two thirds of the passes (rows of 128 nodes, D3Q19 20..120 MB
+  // 0.69..1.18 and 0.60..0.78; D2Q9 263x544 10.3 and 8.3 us a step).
+  if (most == 4 && one < 3 * vec) return false;
   if (most == 2 && p.nx >= 512) return true;
   return bytes >= size_t(Q == 9 ? (most == 4 ? 0 : 40) : (most == 4 ? 40 : 60)) << 20;
 }

@@ -24,12 +24,15 @@ def _boxed(q, n, walls, seed=3):
 # Rows that end in part of a vector and rows that do not, a wavefront's pass and more;
 # test_host_sequence.py checks that these lattices take these forms.
 POPULATIONS = [
-    (9, (129, 17, 1), "fp32", 4, False), (9, (130, 17, 1), "fp32", 4, False), (9, (131, 33, 1), "fp32", 4, False),
-    (9, (256, 16, 1), "fp32", 4, False), (9, (257, 18, 1), "fp32", 4, False), (9, (515, 20, 1), "fp32", 4, False),
+    (9, (129, 17, 1), "fp32", 4, False), (9, (130, 17, 1), "fp32", 4, False),
+    (9, (131, 33, 1), "fp32", 4, False), (9, (256, 16, 1), "fp32", 4, False),
+    (9, (449, 18, 1), "fp32", 4, False), (9, (515, 20, 1), "fp32", 4, False),
     (9, (512, 17, 1), "fp64", 2, False), (9, (641, 16, 1), "fp64", 2, False), (9, (513, 7, 1), "fp64", 1, True),
-    (9, (400, 16, 1), "fp64", 1, False), (19, (129, 66, 67), "fp32", 4, False), (19, (130, 66, 67), "fp32", 4, False),
-    (19, (260, 50, 45), "fp32", 4, False), (19, (193, 48, 48), "fp64", 2, False), (19, (254, 42, 42), "fp64", 2, False),
-    (19, (20, 260, 380), "fp32", 1, True), (19, (157, 155, 150), "fp32", 4, True), (19, (1030, 60, 60), "fp32", 4, True),
+    (9, (400, 16, 1), "fp64", 1, False), (9, (263, 54, 1), "fp32", 1, False),
+    (19, (129, 66, 67), "fp32", 4, False), (19, (130, 66, 67), "fp32", 4, False),
+    (19, (450, 33, 40), "fp32", 4, False), (19, (193, 48, 48), "fp64", 2, False),
+    (19, (254, 42, 42), "fp64", 2, False), (19, (20, 260, 380), "fp32", 1, True),
+    (19, (157, 155, 150), "fp32", 4, True), (19, (1030, 60, 60), "fp32", 4, True),
     (19, (125, 130, 110), "fp64", 2, True), (19, (128, 110, 80), "fp64", 2, True),
 ]
 

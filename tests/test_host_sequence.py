@@ -148,7 +148,7 @@ def test_population_forms(tmp_path):
     from test_gpu_large_forms import POPULATIONS
 
     more = [(19, (128, 128, 128), "fp32", 4, True), (19, (104, 104, 104), "fp64", 2, True), (19, (64, 64, 64), "fp32", 1, False),
-            (19, (129, 16, 16), "fp32", 1, False), (19, (129, 59, 3), "fp64", 1, False), (19, (300, 80, 80), "fp32", 4, False),
+            (19, (129, 16, 16), "fp32", 1, False), (19, (129, 59, 3), "fp64", 1, False), (19, (400, 64, 70), "fp32", 4, False),
             (19, (160, 90, 90), "fp64", 1, True), (19, (256, 256, 256), "fp32", 4, True), (9, (2048, 2048, 1), "fp32", 4, False),
             (9, (1024, 1024, 1), "fp64", 2, False), (9, (140, 4, 1), "fp64", 1, True)]
     standin.run(tmp_path, f"""
