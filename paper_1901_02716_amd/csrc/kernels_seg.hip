@@ -36,38 +36,35 @@ struct Seg3DParams {
   int64_t plane;           // elements per field plane
   double rho_ref;
   double g36x, g36y, g36z;  // 36 dt G / e
-  uint32_t sr_key;
 };
 
 // The links that enter a segment from the node outside it, as seen from its
 // left edge (moving +x); see the mirroring above.
-template <class T>
 struct EdgeLinks {
-  T hxp, p0p, p0m, pp0, pm0;
+  double hxp, p0p, p0m, pp0, pm0;
 };
 
-template <class C>
-__device__ __forceinline__ EdgeLinks<typename C::T> edge_links(typename C::T dr, typename C::T ux, typename C::T uy,
-                                                               typename C::T uz, typename C::T rho_ref) {
-  Links<typename C::T> L;
-  node_links<C>(dr, ux, uy, uz, rho_ref, L);
+__device__ __forceinline__ EdgeLinks edge_links(double dr, double ux, double uy, double uz, double rho_ref) {
+  Links<double> L;
+  node_links<CodecF64>(dr, ux, uy, uz, rho_ref, L);
   return {L.hxp, L.p0p, L.p0m, L.pp0, L.pm0};
 }
 
-template <class C, int KX, int W, bool HALO, int AUX>
-__global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_seg(const typename C::elem* __restrict__ src,
-                                                              typename C::elem* __restrict__ dst, Seg3DParams p) {
-  using T = typename C::T;
-  using E = typename C::elem;
+template <int KX, int W, bool HALO, int AUX>
+__global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_seg(const double* __restrict__ src,
+                                                              double* __restrict__ dst, Seg3DParams p) {
+  using C = CodecF64;
+  using T = double;
+  using E = double;
   using V = RowVec<C, KX>;
   constexpr int SW = 64 * KX;
   constexpr int ROWS = W + 2;
   constexpr int EB = (int)sizeof(E);
   // LDS slots of 4 x SW values: ROWS-1 upward and ROWS-1 downward slots; two
-  // such sets where they fit, so that one barrier per plane suffices.
+  // such sets, so that one barrier per plane suffices.
   constexpr int SLOTS = 2 * (ROWS - 1) * 4 * SW;
-  constexpr bool DB = 2 * SLOTS * (int)sizeof(T) <= 160 * 1024;
-  __shared__ T lds[(DB ? 2 : 1) * SLOTS];
+  static_assert(2 * SLOTS * (int)sizeof(T) <= 160 * 1024, "two sets of slots fit the LDS");
+  __shared__ T lds[2 * SLOTS];
   const int lane = threadIdx.x;
   const int wv = threadIdx.y;
   const int s_up = wv < ROWS - 1 ? wv : ROWS - 2;
@@ -145,7 +142,7 @@ __global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_seg(const typename C:
                           V (&b)[4], E (&h)[4], int set) {
 #pragma clang fp contract(off)
     constexpr bool STORE = decltype(store_c)::value;
-    const int so = DB ? set * SLOTS : 0;
+    const int so = set * SLOTS;
     T* const up = up0 + so;
     T* const dn = dn0 + so;
     T f0[KX], hzp[KX], hzm[KX], hxp[KX], p0p[KX], p0m[KX], hxm[KX], m0p[KX], m0m[KX];
@@ -154,18 +151,15 @@ __global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_seg(const typename C:
 #pragma unroll
     for (int e = 0; e < KX; ++e) {
       Links<T> L;
-      node_links<C>((T)C::dec_scaled(b[0].v[e], 0), (T)C::dec_scaled(b[1].v[e], 1), (T)C::dec_scaled(b[2].v[e], 2),
-                    (T)C::dec_scaled(b[3].v[e], 3), rho_ref, L);
+      node_links<C>(b[0].v[e], b[1].v[e], b[2].v[e], b[3].v[e], rho_ref, L);
       f0[e] = L.f0, hzp[e] = L.hzp, hzm[e] = L.hzm;
       hxp[e] = L.hxp, p0p[e] = L.p0p, p0m[e] = L.p0m;
       hxm[e] = L.hxm, m0p[e] = L.m0p, m0m[e] = L.m0m;
       hyp[e] = L.hyp, pp0[e] = L.pp0, mp0[e] = L.mp0, zpp[e] = L.zpp, zpm[e] = L.zpm;
       hym[e] = L.hym, pm0[e] = L.pm0, mm0[e] = L.mm0, zmp[e] = L.zmp, zmm[e] = L.zmm;
     }
-    EdgeLinks<T> H{};
-    if constexpr (HALO)
-      H = edge_links<C>((T)C::dec_scaled(h[0], 0), mirror * (T)C::dec_scaled(h[1], 1), (T)C::dec_scaled(h[2], 2),
-                        (T)C::dec_scaled(h[3], 3), rho_ref);
+    EdgeLinks H{};
+    if constexpr (HALO) H = edge_links(h[0], mirror * h[1], h[2], h[3], rho_ref);
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
       wprev[f] = wcur[f];
@@ -216,12 +210,10 @@ __global__ __launch_bounds__(64 * (W + 2)) void step_d3q19_seg(const typename C:
         add_sent<T, KX, -1>(fa[0 * SW + x], fa[1 * SW + x], fa[2 * SW + x], fa[3 * SW + x], e, am, ac, ap);
       }
     }
-    if constexpr (!DB) __syncthreads();
     const int zd = zs - 1;
     V o[4] = {};
     if (STORE && out_row) {
-      const int64_t node0 = (int64_t)p.nx * ((int64_t)yrow + (int64_t)p.ny * zwrap(zd)) + xb;
-      finalize_row<C, KX>(am, rho_ref, (T)p.g36x, (T)p.g36y, (T)p.g36z, p.sr_key, node0, o);
+      finalize_row<C, KX>(am, rho_ref, p.g36x, p.g36y, p.g36z, 0u, 0, o);  // (no rounding bits in FP64)
       if constexpr (KX > 1) {
         if (wall_lo || wall_hi) {
 #pragma unroll
@@ -330,15 +322,14 @@ Seg3DShape seg3d_shape(const Layout& L, const StepParams& p, int cus) {
   return best;
 }
 
-template <class C, int KX, int W, bool HALO, int AUX>
+template <int KX, int W, bool HALO, int AUX>
 static hipError_t launch_seg(const void* src, void* dst, const Seg3DParams& sp, hipStream_t s) {
-  using E = typename C::elem;
-  hipLaunchKernelGGL((step_d3q19_seg<C, KX, W, HALO, AUX>), dim3(sp.nblocks), dim3(64, W + 2, 1), 0, s, (const E*)src,
-                     (E*)dst, sp);
+  hipLaunchKernelGGL((step_d3q19_seg<KX, W, HALO, AUX>), dim3(sp.nblocks), dim3(64, W + 2, 1), 0, s,
+                     (const double*)src, (double*)dst, sp);
   return hipGetLastError();
 }
 
-template <class C, int KX, int W>
+template <int KX, int W>
 static hipError_t launch_seg_h(const void* src, void* dst, const Seg3DParams& sp, hipStream_t s) {
   // one segment that spans the row: no node outside it matters (walls), or it wraps by the rotate
   const bool halo = !(sp.nseg == 1 && (!sp.xper || sp.nx == 64 * KX));
@@ -346,20 +337,19 @@ static hipError_t launch_seg_h(const void* src, void* dst, const Seg3DParams& sp
   // 191 us, 201 device-scope, 204 cached), a smaller one with device-scope
   // stores, which leave it there for the next step (128x129x131: 24.7 us, 31.0
   // non-temporal, 25.6 cached), as in the D2Q9 step.
-  const bool stream = 4 * sp.plane * (int64_t)sizeof(typename C::elem) >= (int64_t)kStreamStoreBytes;
+  const bool stream = 4 * sp.plane * (int64_t)sizeof(double) >= (int64_t)kStreamStoreBytes;
   if (stream)
-    return halo ? launch_seg<C, KX, W, true, kStoreStream>(src, dst, sp, s)
-                : launch_seg<C, KX, W, false, kStoreStream>(src, dst, sp, s);
-  return halo ? launch_seg<C, KX, W, true, kStoreDevice>(src, dst, sp, s)
-              : launch_seg<C, KX, W, false, kStoreDevice>(src, dst, sp, s);
+    return halo ? launch_seg<KX, W, true, kStoreStream>(src, dst, sp, s)
+                : launch_seg<KX, W, false, kStoreStream>(src, dst, sp, s);
+  return halo ? launch_seg<KX, W, true, kStoreDevice>(src, dst, sp, s)
+              : launch_seg<KX, W, false, kStoreDevice>(src, dst, sp, s);
 }
 
-template <class C>
 static hipError_t launch_seg_shape(const Seg3DShape& sh, const void* src, void* dst, const Seg3DParams& sp,
                                    hipStream_t s) {
-  if (sh.kx == 1 && sh.w == 14) return launch_seg_h<C, 1, 14>(src, dst, sp, s);
-  if (sh.kx == 1 && sh.w == 6) return launch_seg_h<C, 1, 6>(src, dst, sp, s);
-  if (sh.kx == 2 && sh.w == 6) return launch_seg_h<C, 2, 6>(src, dst, sp, s);
+  if (sh.kx == 1 && sh.w == 14) return launch_seg_h<1, 14>(src, dst, sp, s);
+  if (sh.kx == 1 && sh.w == 6) return launch_seg_h<1, 6>(src, dst, sp, s);
+  if (sh.kx == 2 && sh.w == 6) return launch_seg_h<2, 6>(src, dst, sp, s);
   return hipErrorInvalidValue;
 }
 
@@ -389,8 +379,7 @@ hipError_t launch_step_seg(const Layout& L, const void* src, void* dst, const St
   sp.g36x = 36.0 * p.g[0];
   sp.g36y = 36.0 * p.g[1];
   sp.g36z = 36.0 * p.g[2];
-  sp.sr_key = p.sr_key;
-  return launch_seg_shape<CodecF64>(sh, src, dst, sp, s);
+  return launch_seg_shape(sh, src, dst, sp, s);
 }
 
 }  // namespace maclab

@@ -60,7 +60,8 @@ def test_population_forms(q, n, precision, lanes, streams, walls):
 # not divide the lattice's. test_host_sequence.py checks that they take these forms.
 SEGMENTS = [
     ((64, 60, 50), "", (1, 6, 0, 0)), ((42, 40, 198), "xyz", (1, 6, 0, 0)), ((129, 40, 40), "", (1, 6, 1, 0)),
-    ((199, 155, 14), "xyz", (1, 6, 1, 0)), ((295, 104, 286), "xyz", (1, 6, 1, 1)), ((44, 195, 141), "xyz", (1, 14, 0, 0)),
+    ((199, 155, 14), "xyz", (1, 6, 1, 0)), ((295, 104, 286), "xyz", (1, 6, 1, 1)),
+    ((44, 195, 141), "xyz", (1, 14, 0, 0)),
     ((28, 122, 220), "", (1, 14, 1, 0)), ((130, 129, 131), "xyz", (1, 14, 1, 0)), ((255, 169, 141), "", (1, 14, 1, 0)),
     ((259, 185, 181), "yz", (1, 14, 1, 1)), ((60, 380, 375), "xyz", (1, 14, 0, 1)), ((98, 143, 60), "xy", (2, 6, 0, 0)),
     ((119, 145, 50), "xy", (2, 6, 0, 0)), ((128, 128, 128), "xyz", (2, 6, 0, 0)), ((128, 128, 128), "", (2, 6, 0, 0)),
