@@ -160,6 +160,8 @@ struct Multi2DShape {
 };
 constexpr int kMultiStepsMax = 12;  // steps of one launch
 constexpr int kMultiRowsMin = 4;    // rows a tile stores, at least
+// Whether a launch of so many tiles is within the 2^32 work-items of a grid dimension.
+inline bool multi2d_fits(int64_t tiles, const Multi2DShape& sh) { return tiles * 64 * sh.nw < int64_t(1) << 32; }
 bool multi2d_shape_valid(const Layout& L, const StepParams& p, const Multi2DShape& sh);
 int multi2d_tiles(const Layout& L, const StepParams& p, const Multi2DShape& sh, int halo);
 int multi2d_shapes(const Layout& L, const StepParams& p, int cus, Multi2DShape* out, int max_out);

@@ -232,12 +232,14 @@ static int multi2d_rank(double state_bytes, int precision, int cus, Multi2DShape
     sh.r = t[0];
     sh.nw = t[1];
     for (sh.steps = 2; sh.steps <= kMultiStepsMax && 2 * sh.steps + kMultiRowsMin <= sh.r * sh.nw; ++sh.steps) {
-      const double c = multi2d_cost(state_bytes, tiles(sh), sh, precision, cus);
-      if (c < best_cost) {
+      const int64_t count = tiles(sh);
+      const double c = multi2d_cost(state_bytes, count, sh, precision, cus);
+      if (c < best_cost && multi2d_fits(count, sh)) {
         best_cost = c;
         best = sh;
       }
     }
+    if (best.steps == 0) continue;
     int at = n++;
     for (; at > 0 && cost[at - 1] > best_cost; --at) {
       cost[at] = cost[at - 1];

@@ -1225,6 +1225,7 @@ void batch_multi_items(maclab_batch_t b, const Multi2DShape& m, std::vector<int4
     for (int yt = 0; yt < nyt; ++yt)
       for (int xt = 0; xt < nxt; ++xt) items->push_back(make_int4(i, xt, yt, 0));
   }
+  if (!multi2d_fits((int64_t)items->size(), m)) items->clear();
 }
 
 // Makes the device tables match the current tiling, faces and forces.

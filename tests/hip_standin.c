@@ -51,6 +51,7 @@ void __hipRegisterFunction(void** m, const void* f, char* d, const char* name, u
 }
 
 static dim3_t cfg_grid, cfg_block;
+static int last_error;
 static size_t cfg_lds;
 static void* cfg_stream;
 int __hipPushCallConfiguration(dim3_t grid, dim3_t block, size_t lds, void* stream) {
@@ -63,6 +64,8 @@ int __hipPopCallConfiguration(dim3_t* grid, dim3_t* block, size_t* lds, void** s
 }
 int hipLaunchKernel(const void* f, dim3_t grid, dim3_t block, void** args, size_t lds, void* stream) {
   (void)lds, (void)stream;
+  if ((uint64_t)grid.x * block.x >> 32 || (uint64_t)grid.y * block.y >> 32 || !grid.x || !grid.y || !grid.z)
+    return last_error = 9; /* hipErrorInvalidConfiguration */
   for (int i = 0; i < nkernels; ++i)
     if (kernels[i].f == f) add(kernels[i].name, grid, block, *(const void**)args[0], *(const void**)args[1]);
   return 0;
@@ -80,7 +83,10 @@ int hipSetDevice(int d) { return (void)d, 0; }
 int hipDeviceGetAttribute(int* v, int a, int d) { return (void)a, (void)d, *v = 256, 0; } /* compute units */
 int hipGetSymbolAddress(void** p, const void* s) { return (void)s, *p = (void*)4096, 0; }
 const char* hipGetErrorString(int e) { return e ? "failed on purpose" : "no error"; }
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void) {
+  int e = last_error;
+  return last_error = 0, e;
+}
 int hipEventCreate(void** e) { return *e = (void*)1, 0; }
 int hipEventCreateWithFlags(void** e, unsigned f) { return (void)f, *e = (void*)1, 0; }
 int hipEventDestroy(void* e) { return (void)e, 0; }

@@ -195,3 +195,19 @@ for n, walls, (kx, w, halo, streams) in {SEGMENTS}:
     policy = 2 if streams else 16
     assert rc == 0 and got and tuple(map(int, got.groups())) == (kx, w, halo, policy), (n, walls, log[0][0])
 """)
+
+
+def test_a_batch_of_millions_of_lattices_stays_within_a_grid(tmp_path):
+    """One tile of a thousand threads for each of 4.2 million lattices would be more than
+    2^32 work-items; single steps take 64 for each."""
+    standin.run(tmp_path, """
+import ctypes
+r = standin.load()
+count = 4200000
+c = r.config(9, (3, 3), r.m.FP32)
+cfgs = (r.m.Config * count).from_buffer_copy(bytes(c) * count)
+b = ctypes.c_void_p()
+need = r.lib.maclab_batch_workspace_bytes(cfgs, count)
+assert r.lib.maclab_batch_init(cfgs, count, standin.WORKSPACE, need, ctypes.byref(b)) == 0
+assert r.lib.maclab_batch_step(b, 5) == 0, r.lib.maclab_batch_last_error(b)
+""")
