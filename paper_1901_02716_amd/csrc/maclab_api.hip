@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -1302,6 +1303,18 @@ int batch_launch_steps(maclab_batch_t b, hipStream_t s, int cur, int64_t step, i
   return MACLAB_OK;
 }
 
+// Runs an entry point's body: no exception crosses the ABI. A table that did not fit
+// host memory is built again by the next call.
+template <class F>
+int batch_guarded(maclab_batch_t b, F&& body) {
+  try {
+    return body();
+  } catch (const std::bad_alloc&) {
+    if (b) b->uploaded = false;
+    return bfail(b, MACLAB_EINVAL, "out of host memory");
+  }
+}
+
 // The launches of one graph of n (even) steps: an even number of them, so that
 // a replay begins and ends in buffer 0.
 std::vector<int> graph_launches(int n, int most) {
@@ -1319,14 +1332,12 @@ extern "C" {
 size_t maclab_batch_workspace_bytes(const maclab_config* cfgs, int count) {
   BatchLayout B;
   std::string why;
-  if (batch_layout(cfgs, count, &B, &why) != MACLAB_OK) return 0;
-  return B.total;
+  const int rc = batch_guarded(nullptr, [&] { return batch_layout(cfgs, count, &B, &why); });
+  return rc == MACLAB_OK ? B.total : 0;
 }
 
-int maclab_batch_init(const maclab_config* cfgs, int count, void* workspace, size_t workspace_bytes,
+static int batch_init(const maclab_config* cfgs, int count, void* workspace, size_t workspace_bytes,
                       maclab_batch_t* out) {
-  if (!out) return bfail(nullptr, MACLAB_EINVAL, "out is NULL");
-  *out = nullptr;
   BatchLayout B;
   std::string why;
   int rc = batch_layout(cfgs, count, &B, &why);
@@ -1339,6 +1350,7 @@ int maclab_batch_init(const maclab_config* cfgs, int count, void* workspace, siz
                  workspace_bytes, B.total);
   maclab_batch_t b = new (std::nothrow) maclab_batch_s();
   if (!b) return bfail(nullptr, MACLAB_EINVAL, "maclab_batch_init: out of host memory");
+  std::unique_ptr<maclab_batch_s, void (*)(maclab_batch_t)> owner(b, maclab_batch_destroy);
   b->count = count;
   b->precision = cfgs[0].precision;
   b->rho_ref = cfgs[0].rho_ref;
@@ -1371,10 +1383,7 @@ int maclab_batch_init(const maclab_config* cfgs, int count, void* workspace, siz
   const int bytes = B.L[0].bytes;
   for (int i = 0; i < count; ++i) {
     maclab_s* h = new (std::nothrow) maclab_s();
-    if (!h) {
-      maclab_batch_destroy(b);
-      return bfail(nullptr, MACLAB_EINVAL, "maclab_batch_init: out of host memory");
-    }
+    if (!h) return bfail(nullptr, MACLAB_EINVAL, "maclab_batch_init: out of host memory");
     h->view = true;
     h->cfg = cfgs[i];
     h->cfg.workspace = nullptr;
@@ -1404,18 +1413,21 @@ int maclab_batch_init(const maclab_config* cfgs, int count, void* workspace, siz
   if (e1 == hipSuccess) e1 = hipStreamCreateWithFlags(&b->priv, hipStreamNonBlocking);
   if (e1 == hipSuccess) e1 = hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming);
   if (e1 == hipSuccess) e1 = hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming);
-  if (e1 != hipSuccess) {
-    rc = bfail(nullptr, MACLAB_EHIP, "maclab_batch_init: %s", hipGetErrorString(e1));
-    maclab_batch_destroy(b);
-    return rc;
-  }
+  if (e1 != hipSuccess) return bfail(nullptr, MACLAB_EHIP, "maclab_batch_init: %s", hipGetErrorString(e1));
   // two nodes per lane only if every lattice is wide enough for it and of
   // even width (an odd periodic row cannot be split in pairs)
   b->kx = 2;
   for (int i = 0; i < count; ++i)
     if (B.L[i].nx < 128 || B.L[i].nx % 2) b->kx = 1;
-  *out = b;
+  *out = owner.release();
   return MACLAB_OK;
+}
+
+int maclab_batch_init(const maclab_config* cfgs, int count, void* workspace, size_t workspace_bytes,
+                      maclab_batch_t* out) {
+  if (!out) return bfail(nullptr, MACLAB_EINVAL, "out is NULL");
+  *out = nullptr;
+  return batch_guarded(nullptr, [&] { return batch_init(cfgs, count, workspace, workspace_bytes, out); });
 }
 
 maclab_t maclab_batch_lattice(maclab_batch_t b, int index) {
@@ -1425,9 +1437,7 @@ maclab_t maclab_batch_lattice(maclab_batch_t b, int index) {
 
 int maclab_batch_count(maclab_batch_t b) { return b ? b->count : 0; }
 
-int maclab_batch_step(maclab_batch_t b, int64_t n) {
-  if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
-  if (n < 0) return bfail(b, MACLAB_EINVAL, "negative step count");
+static int batch_step(maclab_batch_t b, int64_t n) {
   int rc = batch_consistent(b);
   if (!rc) rc = batch_sync(b);
   if (rc) return rc;
@@ -1445,9 +1455,10 @@ int maclab_batch_step(maclab_batch_t b, int64_t n) {
       done = 1;
     }
     if (!b->exec) {
+      const std::vector<int> launches = graph_launches(b->graph_steps, most);
       BHIP_TRY(b, hipStreamBeginCapture(b->priv, hipStreamCaptureModeThreadLocal));
       int k = 0;
-      for (int m : graph_launches(b->graph_steps, most)) {
+      for (int m : launches) {
         rc = batch_launch_steps(b, b->priv, k++ & 1, 0, m);
         if (rc) {
           hipGraph_t g = nullptr;
@@ -1478,9 +1489,13 @@ int maclab_batch_step(maclab_batch_t b, int64_t n) {
   return MACLAB_OK;
 }
 
-int maclab_batch_step_separate(maclab_batch_t b, int64_t n) {
+int maclab_batch_step(maclab_batch_t b, int64_t n) {
   if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
   if (n < 0) return bfail(b, MACLAB_EINVAL, "negative step count");
+  return batch_guarded(b, [&] { return batch_step(b, n); });
+}
+
+static int batch_step_separate(maclab_batch_t b, int64_t n) {
   int rc = batch_consistent(b);
   if (rc) return rc;
   std::vector<Fast2DShape> shapes(b->count);
@@ -1503,10 +1518,16 @@ int maclab_batch_step_separate(maclab_batch_t b, int64_t n) {
   return MACLAB_OK;
 }
 
+int maclab_batch_step_separate(maclab_batch_t b, int64_t n) {
+  if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
+  if (n < 0) return bfail(b, MACLAB_EINVAL, "negative step count");
+  return batch_guarded(b, [&] { return batch_step_separate(b, n); });
+}
+
 int maclab_batch_get_tiling(maclab_batch_t b, int out[3]) {
   if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
   if (!out) return bfail(b, MACLAB_EINVAL, "out is NULL");
-  const int rc = batch_sync(b);
+  const int rc = batch_guarded(b, [&] { return batch_sync(b); });
   if (rc) return rc;
   out[0] = b->kx;
   out[1] = b->rows;
@@ -1514,8 +1535,7 @@ int maclab_batch_get_tiling(maclab_batch_t b, int out[3]) {
   return MACLAB_OK;
 }
 
-int maclab_batch_set_tiling(maclab_batch_t b, int kx, int rows) {
-  if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
+static int batch_set_tiling(maclab_batch_t b, int kx, int rows) {
   std::vector<Lattice2D> t;
   std::vector<int4> it;
   int rc = batch_plan(b, kx, rows, &t, &it);  // validates
@@ -1527,6 +1547,11 @@ int maclab_batch_set_tiling(maclab_batch_t b, int kx, int rows) {
   return batch_sync(b);
 }
 
+int maclab_batch_set_tiling(maclab_batch_t b, int kx, int rows) {
+  if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
+  return batch_guarded(b, [&] { return batch_set_tiling(b, kx, rows); });
+}
+
 int maclab_batch_set_graph(maclab_batch_t b, int steps_per_graph) {
   if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
   if (steps_per_graph < 0 || steps_per_graph % 2 || steps_per_graph > 4096)
@@ -1536,23 +1561,11 @@ int maclab_batch_set_graph(maclab_batch_t b, int steps_per_graph) {
   return MACLAB_OK;
 }
 
-int maclab_batch_autotune(maclab_batch_t b, int reps, double* best_ms) {
-  if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
-  if (reps < 1) return bfail(b, MACLAB_EINVAL, "reps must be >= 1");
-  int rc = batch_consistent(b);
-  if (rc) return rc;
-  hipEvent_t e0, e1;
-  BHIP_TRY(b, hipEventCreate(&e0));
-  hipError_t ee = hipEventCreate(&e1);
-  if (ee != hipSuccess) {
-    (void)hipEventDestroy(e0);
-    return bfail(b, MACLAB_EHIP, "hipEventCreate: %s", hipGetErrorString(ee));
-  }
-  const int kx0 = b->kx, rows0 = b->rows;
-  const bool auto0 = b->multi_auto;
-  const Multi2DShape multi0 = b->multi;
+// The tuner's work; e0 and e1 time it.
+static int batch_tune(maclab_batch_t b, int reps, double* best_ms, hipEvent_t e0, hipEvent_t e1) {
+  int rc = MACLAB_OK;
   double best = 1e300, best_multi_ms = 1e300;
-  int bkx = kx0, brows = rows0;
+  int bkx = b->kx, brows = b->rows;
   Multi2DShape best_multi;
   const int cur = b->lat[0]->cur;
   hipError_t he = hipSuccess;
@@ -1611,26 +1624,42 @@ int maclab_batch_autotune(maclab_batch_t b, int reps, double* best_ms) {
       }
     }
   }
-  if (rc || he != hipSuccess) {
+  if (rc) return rc;
+  if (he != hipSuccess) return bfail(b, MACLAB_EHIP, "autotune timing: %s", hipGetErrorString(he));
+  b->kx = bkx;
+  b->rows = brows;
+  b->multi = best_multi_ms < best ? best_multi : Multi2DShape{};
+  if ((rc = batch_sync(b))) return rc;
+  if (best_ms) *best_ms = std::min(best, best_multi_ms);
+  return MACLAB_OK;
+}
+
+int maclab_batch_autotune(maclab_batch_t b, int reps, double* best_ms) {
+  if (!b) return bfail(nullptr, MACLAB_EINVAL, "batch is NULL");
+  if (reps < 1) return bfail(b, MACLAB_EINVAL, "reps must be >= 1");
+  int rc = batch_consistent(b);
+  if (rc) return rc;
+  hipEvent_t e0, e1;
+  BHIP_TRY(b, hipEventCreate(&e0));
+  hipError_t ee = hipEventCreate(&e1);
+  if (ee != hipSuccess) {
     (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
+    return bfail(b, MACLAB_EHIP, "hipEventCreate: %s", hipGetErrorString(ee));
+  }
+  const int kx0 = b->kx, rows0 = b->rows;
+  const bool auto0 = b->multi_auto;
+  const Multi2DShape multi0 = b->multi;
+  rc = batch_guarded(b, [&] { return batch_tune(b, reps, best_ms, e0, e1); });
+  (void)hipEventDestroy(e0);
+  (void)hipEventDestroy(e1);
+  if (rc) {
     b->kx = kx0;
     b->rows = rows0;
     b->multi_auto = auto0;
     b->multi = multi0;
     b->uploaded = false;  // the device tables are a candidate's
-    if (rc) return rc;
-    return bfail(b, MACLAB_EHIP, "autotune timing: %s", hipGetErrorString(he));
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  b->kx = bkx;
-  b->rows = brows;
-  b->multi = best_multi_ms < best ? best_multi : Multi2DShape{};
-  rc = batch_sync(b);
-  if (rc) return rc;
-  if (best_ms) *best_ms = std::min(best, best_multi_ms);
-  return MACLAB_OK;
+  return rc;
 }
 
 void maclab_batch_destroy(maclab_batch_t b) {

@@ -211,3 +211,36 @@ need = r.lib.maclab_batch_workspace_bytes(cfgs, count)
 assert r.lib.maclab_batch_init(cfgs, count, standin.WORKSPACE, need, ctypes.byref(b)) == 0
 assert r.lib.maclab_batch_step(b, 5) == 0, r.lib.maclab_batch_last_error(b)
 """)
+
+
+def test_a_batch_reports_that_host_memory_ran_out(tmp_path):
+    """Tables that do not fit the process's memory are an error code, not an exception
+    across the ABI, and the batch goes on once they fit."""
+    standin.run(tmp_path, """
+import resource
+r = standin.load()
+lib = r.lib
+sizes = [((1 << 19) + i, 1000) for i in range(6)]  # tables of 40 MB
+def limit(mb):
+    used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+    resource.setrlimit(resource.RLIMIT_AS, (resource.RLIM_INFINITY if mb is None else used + (mb << 20), resource.RLIM_INFINITY))
+want = None
+calls = (lambda b: lib.maclab_batch_step(b, 40), lambda b: lib.maclab_batch_get_tiling(b, (r.m.ctypes.c_int * 3)()),
+         lambda b: lib.maclab_batch_set_tiling(b, 1, 4), lambda b: lib.maclab_batch_autotune(b, 1, None))
+for call in calls:
+    for stepped in (False, True):
+        b, fresh = r.batch(sizes, r.m.FP32), r.batch(sizes, r.m.FP32)
+        for h in (b, fresh):
+            assert lib.maclab_batch_set_graph(h, 0) == 0
+            if stepped:
+                assert lib.maclab_batch_step(h, 1) == 0
+        limit(3)
+        rc = call(b)
+        limit(None)
+        assert rc == r.m.EINVAL or (stepped and rc == 0), rc
+        assert rc == 0 or b"out of host memory" in lib.maclab_batch_last_error(b)
+        if rc:
+            assert r.launches(lib.maclab_batch_step, b, 5)[1][0][:3] == r.launches(lib.maclab_batch_step, fresh, 5)[1][0][:3]
+        lib.maclab_batch_destroy(b)
+        lib.maclab_batch_destroy(fresh)
+""")
