@@ -198,28 +198,34 @@ def time_adjoint(T: int, precision: str = "fp32", reps: int = 3):
         b.record(sim.stream)
         torch.cuda.synchronize()
         bwd.append(max(a.elapsed_time(b), (time.perf_counter() - t0) * 1e3))
-    # bare kernels: the reverse step alone on resident buffers
+    # single steps on resident buffers, one per launch in both directions (a sweep takes
+    # several per launch, forward and back)
     sim.set_fields(case.rho, case.u)
-    s0 = sim.save_state()
+    s = [sim.save_state(), sim.new_states(1)]
     adj = [sim.new_adjoint(), sim.new_adjoint()]
-    sim.adjoint_seed(s0, torch.zeros_like(tg), adj[0])
+    sim.adjoint_seed(s[0], torch.zeros_like(tg), adj[0])
     sim.adjoint_reset()
-    n = 500
-    for i in range(20):
-        sim.adjoint_step(s0, adj[i & 1], adj[(i & 1) ^ 1])
-    torch.cuda.synchronize()
-    a, b = ev(), ev()
-    a.record(sim.stream)
-    for i in range(n):
-        sim.adjoint_step(s0, adj[i & 1], adj[(i & 1) ^ 1])
-    b.record(sim.stream)
-    torch.cuda.synchronize()
-    adj_kernel = a.elapsed_time(b) / n
+
+    def single_ms(step, n=500):
+        for i in range(20):
+            step(i & 1)
+        torch.cuda.synchronize()
+        a, b = ev(), ev()
+        a.record(sim.stream)
+        for i in range(n):
+            step(i & 1)
+        b.record(sim.stream)
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) / n
+
+    adj_kernel = single_ms(lambda i: sim.adjoint_step(s[0], adj[i], adj[i ^ 1]))
+    fwd_kernel = single_ms(lambda i: sim.step_external(s[i], s[i ^ 1], i))
     bwd_ms = min(bwd)
     out = {"workload": f"D2Q9 periodic 512^2 nu=0.005 T={T} {precision}, K={math.ceil(math.sqrt(T))}",
            "forward_ms_per_step": round(fwd, 5), "backward_ms": round(bwd_ms, 3),
            "backward_over_T_forward": round(bwd_ms / (T * fwd), 3),
-           "reverse_step_ms": round(adj_kernel, 5), "reverse_over_forward_step": round(adj_kernel / fwd, 3),
+           "reverse_step_ms": round(adj_kernel, 5), "forward_single_step_ms": round(fwd_kernel, 5),
+           "reverse_over_forward_step": round(adj_kernel / fwd_kernel, 3),
            "adjoint_tiling": sim.adjoint_tiling(), "forward_tiling": sim.tiling()}
     sim.close()
     return out

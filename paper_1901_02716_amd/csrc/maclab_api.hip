@@ -1454,8 +1454,8 @@ static int batch_step(maclab_batch_t b, int64_t n) {
       batch_advance(b, 1, 1);
       done = 1;
     }
+    const std::vector<int> launches = graph_launches(b->graph_steps, most);
     if (!b->exec) {
-      const std::vector<int> launches = graph_launches(b->graph_steps, most);
       BHIP_TRY(b, hipStreamBeginCapture(b->priv, hipStreamCaptureModeThreadLocal));
       int k = 0;
       for (int m : launches) {
@@ -1470,7 +1470,15 @@ static int batch_step(maclab_batch_t b, int64_t n) {
       BHIP_TRY(b, hipStreamEndCapture(b->priv, &b->graph));
       BHIP_TRY(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
     }
-    const int64_t reps = (n - last - done) / b->graph_steps;
+    // One replay fewer where that saves launches: those of a graph are not all full, and the
+    // steps left over may need one more for the buffers' sake (200 steps of 512 cavities in
+    // launches of six: 38, not 40; 101.3 us a step, not 104).
+    int64_t reps = (n - last - done) / b->graph_steps;
+    const auto in_all = [&](int64_t r) {
+      const int64_t left = n - done - r * b->graph_steps;
+      return r * (int64_t)launches.size() + (most > 1 ? multi_launches(left, most) + 1 : left);
+    };
+    if (reps > 1 && in_all(reps - 1) < in_all(reps)) --reps;
     BHIP_TRY(b, hipEventRecord(b->ev_in, b->stream));
     BHIP_TRY(b, hipStreamWaitEvent(b->priv, b->ev_in, 0));
     for (int64_t r = 0; r < reps; ++r) BHIP_TRY(b, hipGraphLaunch(b->exec, b->priv));

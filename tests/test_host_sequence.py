@@ -244,3 +244,20 @@ for call in calls:
         lib.maclab_batch_destroy(b)
         lib.maclab_batch_destroy(fresh)
 """)
+
+
+def test_a_batch_call_takes_few_launches_beside_its_graphs(tmp_path):
+    """The steps a batch makes outside its graphs, and the buffer the call ends in."""
+    standin.run(tmp_path, """
+r = standin.load()
+b = r.batch([(300 + i, 400) for i in range(200)], r.m.FP32)
+h = r.m.ctypes.c_void_p(r.lib.maclab_batch_lattice(b, 0))
+assert r.lib.maclab_batch_step(b, 40) == 0  # (the graph is captured)
+at = r.buffer(h)
+for steps in list(range(1, 130)) + [200, 1001]:
+    rc, log = r.launches(r.lib.maclab_batch_step, b, steps)
+    now = r.buffer(h)
+    assert rc == 0 and (now == at) == (steps % 2 == 0) and "multi" not in log[-1][0], steps
+    assert len(log) <= 16, (steps, len(log))  # two graphs of steps at most
+    at = now
+""")
