@@ -53,8 +53,13 @@ struct Vec<T, 1> {
 // What a shifted vector takes from outside the row is replaced: on a periodic
 // axis by the value across the wrap. A fixed node at a row's end is stored back
 // with its own value, so that a lane's nodes are one vector store.
+//
+// Every FMA is written out, so that the populations have the same bits in every form of
+// the kernel: left to the compiler, c.u of a diagonal link and the terms of phi were
+// fused differently from one form to the next.
 template <int Q, class T, int KX, bool TAIL, bool NT>
 __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src, T* __restrict__ dst, BgkParams p) {
+#pragma clang fp contract(off)
   using Lt = Lattice<Q>;
   using V = typename Vec<T, KX>::type;
   const int64_t rows = p.ny * p.nz;
@@ -115,7 +120,7 @@ __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src
           }
       }
     }
-    T r[KX], u0[KX], u1[KX], u2[KX], rho[KX], uu[KX];
+    T r[KX], m0[KX], m1[KX], m2[KX], inv[KX], u0[KX], u1[KX], u2[KX], rho[KX], uu[KX];
 #pragma unroll
     for (int e = 0; e < KX; ++e) {
       // density deviation and momentum (Eqs. (4)-(5) in population form)
@@ -124,16 +129,17 @@ __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src
 #pragma unroll
       for (int a = 0; a < Q; ++a) {
         r[e] += f[a][e];
-        m[0] += (T)Lt::cx[a] * f[a][e];
-        m[1] += (T)Lt::cy[a] * f[a][e];
-        m[2] += (T)Lt::cz[a] * f[a][e];
+        m[0] = fma_t((T)Lt::cx[a], f[a][e], m[0]);
+        m[1] = fma_t((T)Lt::cy[a], f[a][e], m[1]);
+        m[2] = fma_t((T)Lt::cz[a], f[a][e], m[2]);
       }
       // collide with tau = 1: the new populations are the equilibria of the
       // new state (the body force of test 2 enters the momentum)
       rho[e] = rho_ref + r[e];
-      const T inv = (T)1 / rho[e];
-      u0[e] = (m[0] + g[0]) * inv, u1[e] = (m[1] + g[1]) * inv, u2[e] = (m[2] + g[2]) * inv;
-      uu[e] = u0[e] * u0[e] + u1[e] * u1[e] + u2[e] * u2[e];
+      inv[e] = (T)1 / rho[e];
+      m0[e] = m[0] + g[0], m1[e] = m[1] + g[1], m2[e] = m[2] + g[2];
+      u0[e] = m0[e] * inv[e], u1[e] = m1[e] * inv[e], u2[e] = m2[e] * inv[e];
+      uu[e] = fma_t(u2[e], u2[e], fma_t(u0[e], u0[e], u1[e] * u1[e]));
     }
     const bool wall_lo = p.fixed[0] && lo, wall_hi = p.fixed[0] && hi;
     if (KX == 1 && (wall_lo || wall_hi)) continue;
@@ -143,10 +149,17 @@ __global__ __launch_bounds__(256) void bgk_step_kernel(const T* __restrict__ src
       T o[KX];
 #pragma unroll
       for (int e = 0; e < KX; ++e) {
-        const T cu = (T)Lt::cx[a] * u0[e] + (T)Lt::cy[a] * u1[e] + (T)Lt::cz[a] * u2[e];
-        const T phim1 = (T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * uu[e];  // phi_a - 1
+        // c.u: one of a diagonal link's two products m / rho enters unrounded
+        constexpr bool d3 = Q == 19;
+        const int cx = Lt::cx[a], cy = Lt::cy[a], cz = Lt::cz[a];
+        const T cxy = cx && cy ? (d3 && cx < 0 && cy > 0 ? fma_t(m1[e], inv[e], -u0[e])
+                                                         : fma_t((T)cx * m0[e], inv[e], (T)cy * u1[e]))
+                               : fma_t((T)cy, u1[e], (T)cx * u0[e]);
+        const T cu = cz ? fma_t((T)cz * m2[e], inv[e], cxy) : fma_t((T)0, u2[e], cxy);
+        // phi_a - 1 = 3 c.u + 4.5 (c.u)^2 - 1.5 |u|^2
+        const T phim1 = fma_t((T)-1.5, uu[e], fma_t((T)3, cu, ((T)4.5 * cu) * cu));
         // w_a (rho phi_a - rho_ref) = w_a (r + rho (phi_a - 1))
-        o[e] = (T)Lt::wnum[a] * (r[e] + rho[e] * phim1) * (T)(1.0 / 36.0);
+        o[e] = (T)Lt::wnum[a] * fma_t(rho[e], phim1, r[e]) * (T)(1.0 / 36.0);
         if (KX > 1 && ((wall_lo && e == 0) || (wall_hi && i + e == nx - 1))) o[e] = edge[a];
       }
       // device-scope: a state of under 148 MB, so a plane is within a buffer resource's range

@@ -54,6 +54,33 @@ def test_population_forms(q, n, precision, lanes, streams, walls):
     assert rel_l2(u, ou) < tol and rel_l2(rho, orho) < tol
 
 
+# (lattice, nodes, copies along each axis, storage): the first lattice takes one node per
+# lane, the one made of its copies another form.
+COPIES = [
+    (19, (64, 16, 16), (4, 4, 4), "fp32"), (19, (43, 16, 16), (3, 5, 5), "fp32"),
+    (19, (64, 16, 16), (4, 8, 6), "fp32"), (19, (53, 16, 16), (3, 10, 10), "fp32"),
+    (9, (64, 32, 1), (4, 2, 1), "fp32"), (9, (77, 16, 1), (7, 1, 1), "fp32"),
+    (19, (50, 16, 16), (4, 4, 4), "fp64"), (19, (65, 16, 16), (3, 4, 4), "fp64"),
+    (19, (64, 16, 16), (2, 8, 6), "fp64"), (19, (39, 16, 16), (5, 10, 10), "fp64"),
+    (9, (90, 40, 1), (7, 1, 1), "fp64"),
+]
+
+
+@pytest.mark.parametrize("q,n,copies,precision", COPIES)
+def test_population_forms_have_the_same_bits(q, n, copies, precision):
+    case = workloads.random_field(q, n, seed=11, amp=0.05)
+    d = 2 if q == 9 else 3
+    rho, u = np.asarray(case.rho).reshape(n[::-1]), np.asarray(case.u).reshape((d,) + n[::-1])
+    pops = []
+    for c in ((1, 1, 1), copies):
+        m = tuple(a * b for a, b in zip(n, c))
+        sim = BGK(q, m, 0.1, 0.05, precision=precision, body_force=(0.1, -0.2, 0.05))
+        sim.set_fields(np.tile(rho, c[::-1]), np.tile(u, (1,) + c[::-1]))
+        sim.step(3)
+        state = sim.save_state().view(torch.float32 if precision == "fp32" else torch.float64)
+        pops.append(state.reshape(q, -1)[:, : int(np.prod(m))].reshape((q,) + m[::-1]))
+    assert torch.equal(pops[0].repeat((1,) + copies[::-1]), pops[1])
+
 # The FP64 D3Q19 march: (nodes, walls, (nodes per lane, output rows of a workgroup, nodes
 # beside a segment evaluated, streaming stores)). Odd and even widths, with and without
 # padding of the row, a segment that the row ends in or fills; workgroups whose rows do
