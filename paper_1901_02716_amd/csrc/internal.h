@@ -160,6 +160,10 @@ struct Multi2DShape {
 };
 constexpr int kMultiStepsMax = 12;  // steps of one launch
 constexpr int kMultiRowsMin = 4;    // rows a tile stores, at least
+inline int multi2d_steps_max(const Multi2DShape& sh) {
+  const int by_rows = (sh.r * sh.nw - kMultiRowsMin) / 2;
+  return by_rows < kMultiStepsMax ? by_rows : kMultiStepsMax;
+}
 // Whether a launch of so many tiles is within the 2^32 work-items of a grid dimension.
 inline bool multi2d_fits(int64_t tiles, const Multi2DShape& sh) { return tiles * 64 * sh.nw < int64_t(1) << 32; }
 bool multi2d_shape_valid(const Layout& L, const StepParams& p, const Multi2DShape& sh);

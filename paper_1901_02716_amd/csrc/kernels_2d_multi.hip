@@ -183,8 +183,7 @@ bool multi2d_shape_valid(const Layout& L, const StepParams& p, const Multi2DShap
   bool known = false;
   for (const auto& t : kMultiTiles) known |= t[0] == sh.r && t[1] == sh.nw;
   // something of a tile must be left after the overlap
-  return known && sh.steps >= 2 && sh.steps <= kMultiStepsMax && 2 * sh.steps + kMultiRowsMin <= sh.r * sh.nw &&
-         fast2d_supported(L, p);
+  return known && sh.steps >= 2 && sh.steps <= multi2d_steps_max(sh) && fast2d_supported(L, p);
 }
 
 // The steps of a launch for a tile, from a model of the time: a launch costs 3.6 us
@@ -231,7 +230,7 @@ static int multi2d_rank(double state_bytes, int precision, int cus, Multi2DShape
     double best_cost = 1e300;
     sh.r = t[0];
     sh.nw = t[1];
-    for (sh.steps = 2; sh.steps <= kMultiStepsMax && 2 * sh.steps + kMultiRowsMin <= sh.r * sh.nw; ++sh.steps) {
+    for (sh.steps = 2; sh.steps <= multi2d_steps_max(sh); ++sh.steps) {
       const int64_t count = tiles(sh);
       const double c = multi2d_cost(state_bytes, count, sh, precision, cus);
       if (c < best_cost && multi2d_fits(count, sh)) {

@@ -203,7 +203,7 @@ Multi2DShape adjoint_multi_shape(const Layout& L, bool fixed_x, bool fixed_y) {
     Multi2DShape sh;
     sh.r = r;
     sh.nw = 16;
-    for (sh.steps = 2; sh.steps <= kMultiStepsMax && 2 * sh.steps + kMultiRowsMin <= sh.r * sh.nw; ++sh.steps) {
+    for (sh.steps = 2; sh.steps <= multi2d_steps_max(sh); ++sh.steps) {
       const int64_t tiles = adjoint_multi_tiles(L, fixed_x, fixed_y, sh);
       const double per_cu = tiles <= 4 * kCus ? (double)((tiles + kCus - 1) / kCus) : (double)tiles / kCus;
       const double step = per_cu * sh.r * sh.nw * row;

@@ -339,13 +339,16 @@ int multi_chunk(int64_t left, int most) {
   return (int)((left + launches - 1) / launches);
 }
 
-// Launches of a call of n steps ahead of its last step, at most `most` steps each:
-// as few as possible, but so many that the buffers alternate as with single steps.
-// An even n then ends in the buffer it began in, so that a caller's captured call
-// can be replayed.
-int64_t multi_launches(int64_t n, int most) {
+// Launches of a call of n steps ahead of its last step, of `most` steps at most: as few
+// as possible, but so many that the buffers alternate as with single steps. An even
+// n then ends in the buffer it began in, so that a caller's captured call can be replayed.
+// Where the number has the wrong parity, one launch fewer if steps of up to `stretch` a
+// launch allow that (512^2 FP32, 22 steps in launches of five: four of five and six,
+// not six), else one more.
+int64_t multi_launches(int64_t n, int most, int stretch) {
   const int64_t k = (n - 1 + most - 1) / most;
-  return k + ((k + 1 - n) & 1);  // (k + 1 <= n - 1 here: k = n - 1 has the parity)
+  if (!((k + 1 - n) & 1)) return k;
+  return k > 1 && (n - 1 + k - 2) / (k - 1) <= stretch ? k - 1 : k + 1;  // (k < n - 1 here)
 }
 
 // Whether the plan's several steps per launch are taken: a lattice of a batch goes
@@ -490,14 +493,16 @@ int maclab_step(maclab_t h, int64_t n) {
   // Several steps per launch, but the last one alone: the other buffer then holds
   // the state one step before, which maclab_residual compares with.
   const bool several = pl.kernel == 3 && pl.multi.steps > 1 && takes_several(h);
-  for (int64_t k = several ? multi_launches(n, pl.multi.steps) : 0; n > 0; --k) {
+  Multi2DShape multi = pl.multi;
+  if (several) multi.steps = std::min(pl.multi.steps + 1, multi2d_steps_max(multi));
+  for (int64_t k = several ? multi_launches(n, pl.multi.steps, multi.steps) : 0; n > 0; --k) {
     const int m = several && k > 0 ? (int)((n - 1 + k - 1) / k) : 1;
     p.step = (uint64_t)h->steps;
     p.sr_key = sr_key(p.seed, p.step);
     const void* src = h->state[h->cur];
     void* dst = h->state[h->cur ^ 1];
     if (m > 1) {
-      HIP_TRY(h, launch_multi2d(h->L, src, dst, p, pl.multi, m, h->stream));
+      HIP_TRY(h, launch_multi2d(h->L, src, dst, p, multi, m, h->stream));
     } else {
       HIP_TRY(h, launch_plan(h->L, p, pl, src, dst, h->stream));
       HIP_TRY(h, launch_derive_faces(h->L, dst, h->fv, h->stream));
@@ -1476,7 +1481,7 @@ static int batch_step(maclab_batch_t b, int64_t n) {
     int64_t reps = (n - last - done) / b->graph_steps;
     const auto in_all = [&](int64_t r) {
       const int64_t left = n - done - r * b->graph_steps;
-      return r * (int64_t)launches.size() + (most > 1 ? multi_launches(left, most) + 1 : left);
+      return r * (int64_t)launches.size() + (most > 1 ? multi_launches(left, most, most) + 1 : left);
     };
     if (reps > 1 && in_all(reps - 1) < in_all(reps)) --reps;
     BHIP_TRY(b, hipEventRecord(b->ev_in, b->stream));
@@ -1487,7 +1492,7 @@ static int batch_step(maclab_batch_t b, int64_t n) {
     batch_advance(b, reps * b->graph_steps, 0);  // an even number of launches each
     done += reps * b->graph_steps;
   }
-  for (int64_t k = most > 1 ? multi_launches(n - done, most) : 0; done < n; --k) {
+  for (int64_t k = most > 1 ? multi_launches(n - done, most, most) : 0; done < n; --k) {
     const int m = most > 1 && k > 0 ? (int)((n - 1 - done + k - 1) / k) : 1;
     rc = batch_launch_steps(b, b->stream, b->lat[0]->cur, b->lat[0]->steps, m);
     if (rc) return rc;
