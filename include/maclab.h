@@ -192,7 +192,8 @@ int maclab_load_state(maclab_t h, const void* src_device);
 
 /* Kernel and tiling of the step. out[5] = {kernel, W, nyb, nzb, pf}.
  *  kernel 0: general kernel (any shape and boundaries; no tiling to set: D3Q19
- *    runs it as row segments that march in z).
+ *    runs it as row segments that march in z, small FP64 lattices with one
+ *    thread per node).
  *  kernel 1: fast D3Q19, LDS exchange (row pitch 64, 128 or 256: x extent
  *    64, 128 or 256, or between fixed x faces an extent padded to one of
  *    them; FP32 arithmetic): one wavefront per x-row marches in z;
@@ -213,16 +214,18 @@ int maclab_load_state(maclab_t h, const void* src_device);
  * Kernels 1 and 2 and every valid tiling of a kernel give bitwise identical
  * results. A tiling of kernel 3 that was set runs one step per launch; the
  * default and maclab_autotune take several where that is faster, and the
- * tiling reported is that of the single steps. */
+ * tiling reported is that of the single steps: setting it on another handle
+ * gives single steps there. The shape of several steps cannot be read or set; a
+ * handle that is to have it keeps the default or is tuned itself. */
 int maclab_get_tiling(maclab_t h, int out[5]);
 int maclab_set_tiling(maclab_t h, int kernel, int W, int nyb, int nzb, int pf);
 
 /* Times the candidate tilings of this lattice (each launched `reps` times
  * from the current state into the spare buffer, so the simulation does not
- * advance; before each timed launch an untimed pass reads the spare buffer,
- * so that the launch finds its source out of the caches, as a step does)
- * and keeps the fastest; *best_ms (may be NULL) receives its time per step.
- * The spare buffer then holds the state one step ahead, so until the next
+ * advance; before each timed launch the source is copied to the spare buffer
+ * and back, so that the caches hold what they hold after a step; several
+ * steps per launch are timed with half the repetitions) and keeps the fastest;
+ * *best_ms (may be NULL) receives its time per step. The spare buffer then holds the state one step ahead, so until the next
  * step maclab_residual gives the change over that step. Synchronises. */
 int maclab_autotune(maclab_t h, int reps, double* best_ms);
 
@@ -322,13 +325,16 @@ int maclab_get_adjoint_tiling(maclab_t h, int out[3]);
  *                 before the caller's stream (not for MACLAB_S16, whose
  *                 rounding is keyed per step). Results are bitwise those of
  *                 stepping each lattice with maclab_step on the fast D2Q9
- *                 kernels.
+ *                 kernels. As in maclab_step, an even n ends in the buffers it
+ *                 began in.
  *                 MACLAB_EINVAL if a lattice was stepped on its own.
  *  step_separate: the same n steps as one launch per lattice per step (the
  *                 schedule a loop over single lattices would use).
- *  get_tiling:    out[3] = {kx, rows, work items}. set_tiling: kx in {1,2},
- *                 rows >= 4 (a periodic x extent must be a multiple of
- *                 kx). autotune: times every candidate (each launched
+ *  get_tiling:    out[3] = {kx, rows, work items} of the single steps.
+ *                 set_tiling: kx in {1,2}, rows >= 4 (a periodic x extent must
+ *                 be a multiple of kx); from then on the batch takes one step
+ *                 per launch, until autotune. The tiles of several steps
+ *                 cannot be read or set. autotune: times every candidate (each launched
  *                 `reps` times into the spare buffers, so nothing advances;
  *                 an untimed pass over the spare buffers before each timed
  *                 launch leaves the source out of the caches, as in a step),

@@ -2,9 +2,9 @@
 
 ``Batch(problems, precision)`` places every lattice in one workspace;
 ``batch[i]`` is a :class:`Simulation` view of lattice i for boundaries,
-fields and diagnostics; ``step(n)`` advances all lattices with one launch
-per step (captured in HIP graphs), ``step_separate(n)`` with one launch per
-lattice per step. ``cavities(draws)`` builds lid-driven cavities from
+fields and diagnostics; ``step(n)`` advances all lattices with launches of several
+steps (one each after ``set_tiling``), in HIP graphs, ``step_separate(n)`` with one
+launch per lattice per step. ``cavities(draws)`` builds lid-driven cavities from
 ``workloads.batch_draw``.
 """
 from __future__ import annotations

@@ -15,7 +15,7 @@
 // (no row padding), holding the post-collision populations as deviations
 // F_a - w_a rho_ref (FP64 or FP32), so that sums of them stay small, as in
 // the MacLAB state. Fixed (boundary) nodes hold f_eq(rho_b, u_b) in both
-// buffers and are never written by a step.
+// buffers, and a step leaves their values as they are.
 #include "internal.h"
 
 namespace maclab {

@@ -35,8 +35,8 @@ __device__ __forceinline__ int64_t wrap_idx(int64_t v, int64_t n) {
 
 // One thread per destination node; the upstream values come through the
 // cache. Handles every shape, periodic wrap on any axis and fixed faces: D2Q9
-// lattices that are not the fast kernel's, and small FP64 D3Q19 lattices (larger
-// ones and the other storages march in z: kernels_seg.hip, kernels_rows.hip).
+// lattices that are not the fast kernel's, and FP64 D3Q19 lattices of few rows (the
+// others march in z: kernels_seg.hip, kernels_rows.hip).
 template <int Q, class C>
 __global__ __launch_bounds__(256) void step_generic_kernel(const typename C::elem* __restrict__ src,
                                                            typename C::elem* __restrict__ dst,
