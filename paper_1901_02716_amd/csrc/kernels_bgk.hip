@@ -41,8 +41,8 @@ struct Vec<T, 1> {
 // Bound: HBM (2 Q values a node). 16-byte accesses keep four times the bytes in
 // flight per load of a wavefront: D3Q19 FP32 256^3 587 us a step with one node
 // per lane, 485 with four (5.1 of the 6.75 TB/s of a copy; a copy has 2 streams,
-// this 38); 251^3, whose rows end in part of a vector, 870 and 513; D2Q9 1024^2
-// 32 and 15. Fewer workgroups on a CU change the time by under 3%.
+// this 38); 251^3, whose rows end in part of a vector, 884 and 526; D2Q9 1024^2
+// 31 and 13.4. Fewer workgroups on a CU change the time by under 3%.
 //
 // Stores: past the caches for a state that does not stay in the memory-side cache
 // between steps (256^3 485 us, 500 device-scope, 504 cached), else device-scope, which

@@ -13,8 +13,8 @@
 //    registers.
 //  - The links of a node are then summed in the order of the lattice table, as one
 //    thread per node does that loads its 19 upstream nodes; those 76 loads a node are
-//    what this form saves (300x67x93 FP32: 34.3 us a step, 18.7 here; 200x200x120 FP32
-//    99.7, 43.9, S16 104, 45.7). Bound by instructions: about 240 a wavefront and plane.
+//    what this form saves (300x67x93 FP32: 32.7 us a step, 17.8 here; 200x200x120 FP32
+//    84.9, 39.2, S16 88.8, 43.4, split-bf16 95.3, 44.8). Bound by instructions: about 240 a wavefront and plane.
 #include "internal.h"
 
 #include <math.h>
